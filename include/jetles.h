@@ -254,7 +254,8 @@ int jz_batch_advance(jz_batch* b, int nsteps);
 /* Continuous batching: change the resident set between steps.  The step's
  * launches read the member table and the work list from device memory, so
  * the captured graph is replayed as it is (a new capture only when the
- * tables must grow beyond their slots, which double each time).  add: the
+ * tables must grow beyond their slots, which double each time, or when the
+ * first member whose tv_alpha is not 1/2 joins).  add: the
  * solver must match the batch (precision, stages, coefficients, tile shape;
  * periodic, no statistics; grid and state set; JZ_EINVAL / JZ_ESTATE
  * otherwise) and not be a member yet; it joins at the next jz_batch_advance
@@ -263,8 +264,8 @@ int jz_batch_advance(jz_batch* b, int nsteps);
  * on the member's own stream follows the batch steps queued so far (the
  * last ones that include it); the caller keeps the solver.  Neither call
  * waits for the device: the table change is staged in pinned host memory
- * and queued behind the steps in flight (the call waits only when the
- * tables must grow, or when 32 earlier changes are still queued behind
+ * and queued behind the steps in flight (the call waits only when a new
+ * capture follows, or when 32 earlier changes are still queued behind
  * unfinished steps).  A batch may be empty (its steps then do nothing).
  * members: the current member count. */
 int jz_batch_add(jz_batch* b, jz_solver* s);

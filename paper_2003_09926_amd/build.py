@@ -25,14 +25,19 @@ def sources() -> list:
 def build_library(verbose: bool = False, extra: list | None = None) -> str:
     """Compile every HIP source into one shared library (always recompiles)."""
     os.makedirs(LIBDIR, exist_ok=True)
-    objs = []
+    objs, running = [], []
     for src in sources():
         obj = os.path.join(LIBDIR, os.path.basename(src).replace(".hip", ".o"))
         cmd = ["hipcc", *HIPCC_FLAGS, *(extra or []), "-c", src, "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
-        subprocess.check_call(cmd)
+        running.append((cmd, subprocess.Popen(cmd)))   # the sources compile side by side
         objs.append(obj)
+    for cmd, proc in running:
+        if proc.wait() != 0:
+            for _, other in running:
+                other.wait()
+            raise subprocess.CalledProcessError(proc.returncode, cmd)
     tmp = LIB + ".tmp"
     cmd = ["hipcc", f"--offload-arch={ARCH}", "-shared", "-fPIC", *objs, "-o", tmp]
     if verbose:

@@ -4,18 +4,25 @@
 
 namespace jz {
 
-template <int BX, int BY>
-static hipError_t launch_shape64(const StageArgs& a, const int* flag, int mode, int nblocks, hipStream_t st) {
+template <int BX, int BY, bool HALF>
+static hipError_t launch_shape64_as(const StageArgs& a, const int* flag, int mode, int nblocks, hipStream_t st) {
   const dim3 grid(nblocks), block(stage_threads<double, BX, BY>());
   switch (mode) {
-    case 0: hipLaunchKernelGGL((stage_kernel<double, double, double, false, BX, BY, 0>), grid, block, 0, st, a, flag); break;
-    case 1: hipLaunchKernelGGL((stage_kernel<double, double, double, false, BX, BY, 1>), grid, block, 0, st, a, flag); break;
-    case 2: hipLaunchKernelGGL((stage_kernel<double, double, double, false, BX, BY, 2>), grid, block, 0, st, a, flag); break;
-    case 3: hipLaunchKernelGGL((stage_kernel<double, double, double, false, BX, BY, 3>), grid, block, 0, st, a, flag); break;
-    case 4: hipLaunchKernelGGL((stage_kernel<double, double, double, false, BX, BY, 4>), grid, block, 0, st, a, flag); break;
+    case 0: hipLaunchKernelGGL((stage_kernel<double, double, double, false, BX, BY, 0, HALF>), grid, block, 0, st, a, flag); break;
+    case 1: hipLaunchKernelGGL((stage_kernel<double, double, double, false, BX, BY, 1, HALF>), grid, block, 0, st, a, flag); break;
+    case 2: hipLaunchKernelGGL((stage_kernel<double, double, double, false, BX, BY, 2, HALF>), grid, block, 0, st, a, flag); break;
+    case 3: hipLaunchKernelGGL((stage_kernel<double, double, double, false, BX, BY, 3, HALF>), grid, block, 0, st, a, flag); break;
+    case 4: hipLaunchKernelGGL((stage_kernel<double, double, double, false, BX, BY, 4, HALF>), grid, block, 0, st, a, flag); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
+}
+
+// tv_alpha = 1/2, or any other exponent (see node_scales)
+template <int BX, int BY>
+static hipError_t launch_shape64(const StageArgs& a, const int* flag, int mode, int nblocks, hipStream_t st) {
+  return a.ph.alpha_half ? launch_shape64_as<BX, BY, true>(a, flag, mode, nblocks, st)
+                         : launch_shape64_as<BX, BY, false>(a, flag, mode, nblocks, st);
 }
 
 // Supported workgroup shapes (bx x by threads); the tile is (bx-4) x (by-4).
@@ -45,22 +52,22 @@ int stage_wg_per_cu_fp64(int bx, int by) {
   int per_cu = 0;
   hipError_t e = hipErrorInvalidValue;
   if (bx == 32 && by == 16)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, stage_kernel<double, double, double, false, 32, 16, 0>, stage_threads<double, 32, 16>(), 0);
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, stage_kernel<double, double, double, false, 32, 16, 0, true>, stage_threads<double, 32, 16>(), 0);
   else if (bx == 64 && by == 8)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, stage_kernel<double, double, double, false, 64, 8, 0>, stage_threads<double, 64, 8>(), 0);
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, stage_kernel<double, double, double, false, 64, 8, 0, true>, stage_threads<double, 64, 8>(), 0);
   else if (bx == 16 && by == 32)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, stage_kernel<double, double, double, false, 16, 32, 0>, stage_threads<double, 16, 32>(), 0);
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, stage_kernel<double, double, double, false, 16, 32, 0, true>, stage_threads<double, 16, 32>(), 0);
   else if (bx == 32 && by == 8)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, stage_kernel<double, double, double, false, 32, 8, 0>, stage_threads<double, 32, 8>(), 0);
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, stage_kernel<double, double, double, false, 32, 8, 0, true>, stage_threads<double, 32, 8>(), 0);
   else if (bx == 16 && by == 16)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, stage_kernel<double, double, double, false, 16, 16, 0>, stage_threads<double, 16, 16>(), 0);
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, stage_kernel<double, double, double, false, 16, 16, 0, true>, stage_threads<double, 16, 16>(), 0);
 
   else if (bx == 36 && by == 12)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, stage_kernel<double, double, double, false, 36, 12, 0>, stage_threads<double, 36, 12>(), 0);
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, stage_kernel<double, double, double, false, 36, 12, 0, true>, stage_threads<double, 36, 12>(), 0);
   else if (bx == 20 && by == 20)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, stage_kernel<double, double, double, false, 20, 20, 0>, stage_threads<double, 20, 20>(), 0);
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, stage_kernel<double, double, double, false, 20, 20, 0, true>, stage_threads<double, 20, 20>(), 0);
   else if (bx == 20 && by == 16)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, stage_kernel<double, double, double, false, 20, 16, 0>, stage_threads<double, 20, 16>(), 0);
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, stage_kernel<double, double, double, false, 20, 16, 0, true>, stage_threads<double, 20, 16>(), 0);
 
   return e == hipSuccess ? per_cu : 0;
 }
@@ -68,10 +75,10 @@ int stage_wg_per_cu_fp64(int bx, int by) {
 // ---------------------------------------------------------------------------
 // persistent batch launches (FP64)
 // ---------------------------------------------------------------------------
-template <int BX, int BY, int MODE>
+template <int BX, int BY, int MODE, bool HALF>
 static hipError_t batch_one64(const BlockDesc* d, const int* off, BatchCtl* ctl, int stage, int ns, double alpha,
                               hipStream_t st) {
-  auto kern = stage_batch_kernel<double, double, double, false, BX, BY, MODE>;
+  auto kern = stage_batch_kernel<double, double, double, false, BX, BY, MODE, HALF>;
   int per_cu = 0, dev = 0, ncu = 0;
   hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, stage_threads<double, BX, BY>(), 0);
   if (e != hipSuccess) return e;
@@ -85,16 +92,24 @@ static hipError_t batch_one64(const BlockDesc* d, const int* off, BatchCtl* ctl,
   return hipGetLastError();
 }
 
-template <int BX, int BY>
-static hipError_t batch_shape64(const BlockDesc* d, const int* off, BatchCtl* ctl, int stage, int ns, double alpha,
+template <int BX, int BY, bool HALF>
+static hipError_t batch_shape64_as(const BlockDesc* d, const int* off, BatchCtl* ctl, int stage, int ns, double alpha,
                                 hipStream_t st) {
   const int mode = (stage == 0 ? 1 : 0) | (stage == ns - 1 ? 2 : 0);
   switch (mode) {
-    case 0: return batch_one64<BX, BY, 0>(d, off, ctl, stage, ns, alpha, st);
-    case 1: return batch_one64<BX, BY, 1>(d, off, ctl, stage, ns, alpha, st);
-    case 2: return batch_one64<BX, BY, 2>(d, off, ctl, stage, ns, alpha, st);
+    case 0: return batch_one64<BX, BY, 0, HALF>(d, off, ctl, stage, ns, alpha, st);
+    case 1: return batch_one64<BX, BY, 1, HALF>(d, off, ctl, stage, ns, alpha, st);
+    case 2: return batch_one64<BX, BY, 2, HALF>(d, off, ctl, stage, ns, alpha, st);
     default: return hipErrorInvalidValue;  // batches take at least two stages
   }
+}
+
+// half: every member has tv_alpha = 1/2 (otherwise the general kernel serves all of them)
+template <int BX, int BY>
+static hipError_t batch_shape64(const BlockDesc* d, const int* off, BatchCtl* ctl, int stage, int ns, double alpha,
+                                bool half, hipStream_t st) {
+  return half ? batch_shape64_as<BX, BY, true>(d, off, ctl, stage, ns, alpha, st)
+              : batch_shape64_as<BX, BY, false>(d, off, ctl, stage, ns, alpha, st);
 }
 
 bool batch64_shape_supported(int bx, int by) {
@@ -103,12 +118,12 @@ bool batch64_shape_supported(int bx, int by) {
 }
 
 hipError_t launch_stage_batch_fp64(const BlockDesc* d, const int* off, BatchCtl* ctl, int stage, int ns, double alpha,
-                                   int bx, int by, hipStream_t st) {
-  if (bx == 32 && by == 16) return batch_shape64<32, 16>(d, off, ctl, stage, ns, alpha, st);
-  if (bx == 16 && by == 16) return batch_shape64<16, 16>(d, off, ctl, stage, ns, alpha, st);
-  if (bx == 36 && by == 12) return batch_shape64<36, 12>(d, off, ctl, stage, ns, alpha, st);
-  if (bx == 20 && by == 20) return batch_shape64<20, 20>(d, off, ctl, stage, ns, alpha, st);
-  if (bx == 20 && by == 16) return batch_shape64<20, 16>(d, off, ctl, stage, ns, alpha, st);
+                                   int bx, int by, bool half, hipStream_t st) {
+  if (bx == 32 && by == 16) return batch_shape64<32, 16>(d, off, ctl, stage, ns, alpha, half, st);
+  if (bx == 16 && by == 16) return batch_shape64<16, 16>(d, off, ctl, stage, ns, alpha, half, st);
+  if (bx == 36 && by == 12) return batch_shape64<36, 12>(d, off, ctl, stage, ns, alpha, half, st);
+  if (bx == 20 && by == 20) return batch_shape64<20, 20>(d, off, ctl, stage, ns, alpha, half, st);
+  if (bx == 20 && by == 16) return batch_shape64<20, 16>(d, off, ctl, stage, ns, alpha, half, st);
   return hipErrorInvalidValue;
 }
 

@@ -53,45 +53,11 @@
 
 #include <stdint.h>
 #include <type_traits>
-#include "jz_internal.h"
+#include "jz_node.h"
 
 namespace jz {
 
 namespace {
-
-template <typename Rl>
-struct Prim {
-  Rl u, v, w, T, p;
-};
-
-template <typename Rl>
-__device__ inline Prim<Rl> primitives(const Rl q[5], Rl gm1, Rl gamma) {
-  Prim<Rl> r;
-  const Rl rinv = rcp_pos(q[0]);
-  r.u = q[1] * rinv;
-  r.v = q[2] * rinv;
-  r.w = q[3] * rinv;
-  r.p = gm1 * (q[4] - Rl(0.5) * q[0] * (r.u * r.u + r.v * r.v + r.w * r.w));
-  r.T = gamma * r.p * rinv;
-  return r;
-}
-
-// J^(-1/3) (the filter width of a cell of volume 1/J): float seed from the
-// hardware log2/exp2, then two Newton steps r <- r + r (1 - J r^3) / 3 in FP64,
-// which square the relative error twice (1e-7 -> 1e-14 -> below rounding).
-__device__ inline double inv_cbrt(double J) {
-  const float jf = (float)J;
-  double r = (double)__builtin_amdgcn_exp2f(-__builtin_amdgcn_logf(jf) * (1.0f / 3.0f));
-  r = r + r * (1.0 - J * r * r * r) * (1.0 / 3.0);
-  r = r + r * (1.0 - J * r * r * r) * (1.0 / 3.0);
-  return r;
-}
-
-// J^(-1/3) in float: hardware log2/exp2 seed and one Newton step
-__device__ inline float inv_cbrt(float J) {
-  float r = __builtin_amdgcn_exp2f(-__builtin_amdgcn_logf(J) * (1.0f / 3.0f));
-  return r + r * (1.0f - J * r * r * r) * (1.0f / 3.0f);
-}
 
 // A register copy the compiler cannot fold into its source: the result gets
 // registers of its own (early clobber), distinct from the operand's.
@@ -251,7 +217,7 @@ constexpr int lds_pitch() {
 // Partial norms and lambda maxima go to slot lt, so the reductions do not
 // depend on how tiles are scheduled.  Every thread of the workgroup calls it;
 // PERSIST: called from the persistent batch kernel's tile loop.
-template <typename Rl, typename TIn, typename TOut, bool MET32, int BX, int BY, int MODE, bool PERSIST>
+template <typename Rl, typename TIn, typename TOut, bool MET32, int BX, int BY, int MODE, bool HALF, bool PERSIST>
 __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
   constexpr int NT = stage_threads<Rl, BX, BY>();  // threads of the workgroup
   constexpr int TI = BX - 4, TJ = BY - 4;
@@ -576,7 +542,6 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
         }
         if (s + 2 < kend + 1) met.load(node(s + 2), Mn, MJn);
       }
-      const Rl J = (Rl)Jg;
       const Rl(*Pg)[NS] = sPr[ZREG ? 0 : slot_g];
       // Every primitive this column needs from the three planes, read in one
       // batch: the memory clobber keeps all the reads ahead of the arithmetic,
@@ -599,67 +564,8 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
         }
       }
       asm volatile("" ::: "memory");
-      // chain rule d phi / d x_a = J sum_d S^d_a delta_d phi, with the 1/2 of
-      // the centred difference folded into the metric factor
-      Rl hm[9];
-#pragma unroll
-      for (int k = 0; k < 9; ++k) hm[k] = (Rl(0.5) * J) * m[k];
-      Rl gr[4][3];  // gr[q][a] = d phi_q / d x_a for phi = u, v, w, T
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const Rl dxi = nxp[q] - nxm[q];
-        const Rl deta = nyp[q] - nym[q];
-        const Rl dzeta = nzp[q] - nzm[q];
-#pragma unroll
-        for (int a = 0; a < 3; ++a) gr[q][a] = hm[a] * dxi + hm[3 + a] * deta + hm[6 + a] * dzeta;
-      }
-      const Rl uu[3] = {ctr[0], ctr[1], ctr[2]};
-      const Rl T = ctr[3], p = ctr[4];
-      const Rl asnd = sqrt_pos(T);
-      const Rl mu = div_pos((Rl)ph.mu_suth * T * asnd, T + (Rl)ph.suth_s);
-      // Smagorinsky: |S| = sqrt(2 S_ab S_ab), Delta = J^(-1/3)
-      const Rl s01 = gr[0][1] + gr[1][0], s02 = gr[0][2] + gr[2][0], s12 = gr[1][2] + gr[2][1];
-      const Rl ss2 = Rl(2) * (gr[0][0] * gr[0][0] + gr[1][1] * gr[1][1] + gr[2][2] * gr[2][2]) +
-                     (s01 * s01 + s02 * s02 + s12 * s12);
-      const Rl smag = ss2 > Rl(0) ? sqrt_pos(ss2) : Rl(0);
-      const Rl delta = inv_cbrt(J);
-      const Rl mut = Qg[0] * (Rl)ph.cs2 * delta * delta * smag;
-      const Rl kap = (Rl)ph.kap_lam * mu + (Rl)ph.kap_turb * mut;
-      const Rl mue = mu + mut;
-      const Rl div23 = (Rl(2) / Rl(3)) * (gr[0][0] + gr[1][1] + gr[2][2]);
-      // Fhat^d = S^d . (E - V) for each direction d: the inviscid part through
-      // the contravariant velocity U^d = S^d . u (rho U, rho u_r U + S^d_r p,
-      // (e + p) U), the viscous part through the symmetric stress tensor and
-      // the energy column w_a = u_r tau_ra - q_a (q_a = -kappa dT/dx_a).
-      // Every multiply-add is an explicit fma and nothing else is contracted,
-      // so that each instantiation of this code (shapes, stages, the batch
-      // kernel) rounds the same way and their results stay bitwise equal.
-      Rl F[3][5], Uc[3];
-      {
-#pragma clang fp contract(off)
-        const Rl txx = mue * fma(Rl(2), gr[0][0], -div23), tyy = mue * fma(Rl(2), gr[1][1], -div23);
-        const Rl tzz = mue * fma(Rl(2), gr[2][2], -div23);
-        const Rl txy = mue * s01, txz = mue * s02, tyz = mue * s12;
-        const Rl tau[3][3] = {{txx, txy, txz}, {txy, tyy, tyz}, {txz, tyz, tzz}};
-        Rl wv[3];
-#pragma unroll
-        for (int a = 0; a < 3; ++a)
-          wv[a] = fma(kap, gr[3][a], fma(uu[2], tau[2][a], fma(uu[1], tau[1][a], uu[0] * tau[0][a])));
-        const Rl ep = Qg[4] + p;
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-          const Rl sx = m[3 * d], sy = m[3 * d + 1], sz = m[3 * d + 2];
-          const Rl U = fma(sz, uu[2], fma(sy, uu[1], sx * uu[0]));
-          Uc[d] = U;
-          F[d][0] = Qg[0] * U;
-#pragma unroll
-          for (int r = 0; r < 3; ++r) {
-            const Rl vis = fma(sz, tau[r][2], fma(sy, tau[r][1], sx * tau[r][0]));
-            F[d][1 + r] = fma(Qg[1 + r], U, fma(m[3 * d + r], p, -vis));
-          }
-          F[d][4] = fma(ep, U, -fma(sz, wv[2], fma(sy, wv[1], sx * wv[0])));
-        }
-      }
+      Rl F[3][5], Uc[3], asnd;
+      node_fluxes(ph, m, Jg, Qg, ctr, nxm, nxp, nym, nyp, nzm, nzp, F, Uc, asnd);
 #pragma unroll
       for (int v = 0; v < 5; ++v) {
         sFx[v][c] = F[0][v];
@@ -669,50 +575,16 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
       if constexpr (COMPACT && BASE == 0) {
         if (upd) update_loads();
       }
-      // Spectral radii and anisotropic dissipation scales.  With
-      // lambda^d = J L^d, L^d = |U^d| + a |S^d|, the scale
-      // sigma^d = phi^d lambda^d / J = phi^d L^d (phi depends only on ratios
-      // of the radii), so J drops out.
-      Rl lam[3];  // L^d
-#pragma unroll
-      for (int d = 0; d < 3; ++d) {
-#pragma clang fp contract(off)
-        const Rl sx = m[3 * d], sy = m[3 * d + 1], sz = m[3 * d + 2];
-        lam[d] = fma(asnd, sqrt_pos(fma(sz, sz, fma(sy, sy, sx * sx))), fabs(Uc[d]));
-      }
       Rl sig[3];
-      if (ph.alpha_half) {
-        // phi^d L^d = L^d + sum_{e != d} sqrt(L^e L^d) = sqrt(L^d) sum_e sqrt(L^e)
-        const Rl r0 = sqrt_pos(lam[0]), r1 = sqrt_pos(lam[1]), r2 = sqrt_pos(lam[2]);
-        const Rl rs = r0 + r1 + r2;
-        sig[0] = r0 * rs;
-        sig[1] = r1 * rs;
-        sig[2] = r2 * rs;
-      } else {
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-          Rl phi = 1;
-#pragma unroll
-          for (int e = 0; e < 3; ++e)
-            if (e != d) phi += (Rl)pow((double)lam[e] / (double)lam[d], ph.tv_alpha);
-          sig[d] = phi * lam[d];
-        }
-      }
+      node_scales<HALF>(ph, m, Uc, asnd, sig);
       sSx[c] = sig[0];
       sSy[c] = sig[1];
       sigg = sig[2];
-      // pressure sensors |p+ - 2p + p-| / (p+ + 2p + p-) along xi, eta, zeta,
-      // the three divisions through one reciprocal of the product of the
-      // (positive) denominators
-      {
-        const Rl ax = fabs(nxp[4] - Rl(2) * p + nxm[4]), bx = nxp[4] + Rl(2) * p + nxm[4];
-        const Rl ay = fabs(nyp[4] - Rl(2) * p + nym[4]), by = nyp[4] + Rl(2) * p + nym[4];
-        const Rl az = fabs(nzp[4] - Rl(2) * p + nzm[4]), bz = nzp[4] + Rl(2) * p + nzm[4];
-        const Rl byz = by * bz, r = rcp_pos(bx * byz);
-        sNx[c] = ax * byz * r;
-        sNy[c] = ay * (bx * bz) * r;
-        nug = az * (bx * by) * r;
-      }
+      Rl nu[3];
+      node_sensors(ctr[4], nxm[4], nxp[4], nym[4], nyp[4], nzm[4], nzp[4], nu);
+      sNx[c] = nu[0];
+      sNy[c] = nu[1];
+      nug = nu[2];
     }
 
     // ---- owned columns, before the barrier: the zeta face between planes s
@@ -724,14 +596,11 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
       if constexpr (!(COMPACT && BASE == 0)) {
         if (upd) update_loads();
       }
-      const Rl e2 = k2 * fmax(nus, nug);
-      const Rl e4 = fmax(Rl(0), k4 - e2);
-      const Rl sg = Rl(0.5) * (sigs + sigg);
+      Rl e2, e4, sg;
+      face_coefs(k2, k4, nus, nug, sigs, sigg, e2, e4, sg);
 #pragma unroll
-      for (int v = 0; v < 5; ++v) {
-        const Rl d3 = (Ql[v] - Qm[v]) - Rl(3) * (Qg[v] - Qs[v]);
-        Hp[v] = Rl(0.5) * (Fzs[v] + Fzg[v]) - sg * (e2 * (Qg[v] - Qs[v]) - e4 * d3);
-      }
+      for (int v = 0; v < 5; ++v)
+        Hp[v] = Rl(0.5) * (Fzs[v] + Fzg[v]) - face_diss(e2, e4, sg, Qm[v], Qs[v], Qg[v], Ql[v]);
     }
     __syncthreads();
 
@@ -744,14 +613,11 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
     typedef __attribute__((address_space(3))) const Rl* lds_ptr;
     auto inplane = [&](int cc, int vb, int ve, Rl Rr[5]) {
       // xi faces cc-1/2 and cc+1/2, eta faces cc-P/2 and cc+P/2 (slots)
-      const Rl e2xp = k2 * fmax(sNx[cc], sNx[cc + 1]);
-      const Rl e2xm = k2 * fmax(sNx[cc - 1], sNx[cc]);
-      const Rl e4xp = fmax(Rl(0), k4 - e2xp), e4xm = fmax(Rl(0), k4 - e2xm);
-      const Rl sgxp = Rl(0.5) * (sSx[cc] + sSx[cc + 1]), sgxm = Rl(0.5) * (sSx[cc - 1] + sSx[cc]);
-      const Rl e2yp = k2 * fmax(sNy[cc], sNy[cc + P]);
-      const Rl e2ym = k2 * fmax(sNy[cc - P], sNy[cc]);
-      const Rl e4yp = fmax(Rl(0), k4 - e2yp), e4ym = fmax(Rl(0), k4 - e2ym);
-      const Rl sgyp = Rl(0.5) * (sSy[cc] + sSy[cc + P]), sgym = Rl(0.5) * (sSy[cc - P] + sSy[cc]);
+      Rl e2xp, e4xp, sgxp, e2xm, e4xm, sgxm, e2yp, e4yp, sgyp, e2ym, e4ym, sgym;
+      face_coefs(k2, k4, sNx[cc], sNx[cc + 1], sSx[cc], sSx[cc + 1], e2xp, e4xp, sgxp);
+      face_coefs(k2, k4, sNx[cc - 1], sNx[cc], sSx[cc - 1], sSx[cc], e2xm, e4xm, sgxm);
+      face_coefs(k2, k4, sNy[cc], sNy[cc + P], sSy[cc], sSy[cc + P], e2yp, e4yp, sgyp);
+      face_coefs(k2, k4, sNy[cc - P], sNy[cc], sSy[cc - P], sSy[cc], e2ym, e4ym, sgym);
 #pragma unroll UNR
       for (int v = vb; v < ve; ++v) {
         // The empty asm hides the array base, so that every neighbour
@@ -767,10 +633,10 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
         const Rl qyp = q[3 * P], qypp = q[4 * P], qym = q[P], qymm = q[0];
         const Rl fxm = fx[0], fxp = fx[2], fym = fy[0], fyp = fy[2 * P];
         asm volatile("" ::: "memory");  // all reads of the trip issued together
-        const Rl dxp = sgxp * (e2xp * (qxp - q0) - e4xp * ((qxpp - qxm) - Rl(3) * (qxp - q0)));
-        const Rl dxm = sgxm * (e2xm * (q0 - qxm) - e4xm * ((qxp - qxmm) - Rl(3) * (q0 - qxm)));
-        const Rl dyp = sgyp * (e2yp * (qyp - q0) - e4yp * ((qypp - qym) - Rl(3) * (qyp - q0)));
-        const Rl dym = sgym * (e2ym * (q0 - qym) - e4ym * ((qyp - qymm) - Rl(3) * (q0 - qym)));
+        const Rl dxp = face_diss(e2xp, e4xp, sgxp, qxm, q0, qxp, qxpp);
+        const Rl dxm = face_diss(e2xm, e4xm, sgxm, qxmm, qxm, q0, qxp);
+        const Rl dyp = face_diss(e2yp, e4yp, sgyp, qym, q0, qyp, qypp);
+        const Rl dym = face_diss(e2ym, e4ym, sgym, qymm, qym, q0, qyp);
         const Rl cx = Rl(0.5) * (fxp - fxm);
         const Rl cy = Rl(0.5) * (fyp - fym);
 #pragma unroll
@@ -945,11 +811,11 @@ constexpr int stage_waves_per_eu() {
 }
 
 // Single block: one workgroup per tile, tiles spread XCD by XCD.
-template <typename Rl, typename TIn, typename TOut, bool MET32, int BX, int BY, int MODE>
+template <typename Rl, typename TIn, typename TOut, bool MET32, int BX, int BY, int MODE, bool HALF>
 __global__ __launch_bounds__((stage_threads<Rl, BX, BY>()))
 __attribute__((amdgpu_waves_per_eu(stage_waves_per_eu<Rl, BX, BY, MODE>()))) void stage_kernel(StageArgs A, const int* __restrict__ flag) {
   if (*flag) return;  // a failed step froze the state
-  stage_tile<Rl, TIn, TOut, MET32, BX, BY, MODE, false>(A, xcd_remap(blockIdx.x, gridDim.x));
+  stage_tile<Rl, TIn, TOut, MET32, BX, BY, MODE, HALF, false>(A, xcd_remap(blockIdx.x, gridDim.x));
 }
 
 // Many blocks in one persistent launch.  The tiles of all blocks form one
@@ -960,7 +826,7 @@ __attribute__((amdgpu_waves_per_eu(stage_waves_per_eu<Rl, BX, BY, MODE>()))) voi
 // the slot's counter, so a workgroup that drew short tiles takes more of
 // them, and every workgroup exits once its slot's share is claimed.  The
 // grid is at least kBatchSlots workgroups, so every slot is served.
-template <typename Rl, typename TIn, typename TOut, bool MET32, int BX, int BY, int MODE>
+template <typename Rl, typename TIn, typename TOut, bool MET32, int BX, int BY, int MODE, bool HALF>
 __global__ __launch_bounds__((stage_threads<Rl, BX, BY>()))
 __attribute__((amdgpu_waves_per_eu(stage_waves_per_eu<Rl, BX, BY, MODE>()))) void stage_batch_kernel(const BlockDesc* __restrict__ desc,
                                                              const int* __restrict__ tile_off,
@@ -1007,7 +873,7 @@ __attribute__((amdgpu_waves_per_eu(stage_waves_per_eu<Rl, BX, BY, MODE>()))) voi
     A.nchunks = D.nchunks;
     A.in = D.in;
     A.ph = D.ph;
-    stage_tile<Rl, TIn, TOut, MET32, BX, BY, MODE, true>(A, g - tile_off[a]);
+    stage_tile<Rl, TIn, TOut, MET32, BX, BY, MODE, HALF, true>(A, g - tile_off[a]);
   }
 }
 
