@@ -255,7 +255,8 @@ int jz_batch_advance(jz_batch* b, int nsteps);
  * launches read the member table and the work list from device memory, so
  * the captured graph is replayed as it is (a new capture only when the
  * tables must grow beyond their slots, which double each time, or when the
- * first member whose tv_alpha is not 1/2 joins).  add: the
+ * first member with another tv_alpha than 1/2, or with planes of more than
+ * 53 million nodes, joins).  add: the
  * solver must match the batch (precision, stages, coefficients, tile shape;
  * periodic, no statistics; grid and state set; JZ_EINVAL / JZ_ESTATE
  * otherwise) and not be a member yet; it joins at the next jz_batch_advance

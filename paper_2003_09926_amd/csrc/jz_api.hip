@@ -24,9 +24,9 @@ int stage_wg_per_cu_fp64(int bx, int by);
 int stage_wg_per_cu_fp32(int bx, int by);
 bool batch32_shape_supported(int bx, int by);
 hipError_t launch_stage_batch_fp64(const BlockDesc* d, const int* off, BatchCtl* ctl, int stage, int ns, double alpha,
-                                   int bx, int by, bool half, hipStream_t st);
+                                   int bx, int by, bool fast, hipStream_t st);
 hipError_t launch_stage_batch_fp32(const BlockDesc* d, const int* off, BatchCtl* ctl, int stage, int ns, double alpha,
-                                   int bx, int by, bool half, hipStream_t st);
+                                   int bx, int by, bool fast, hipStream_t st);
 hipError_t launch_finalize_batch(const BlockDesc* desc, BatchCtl* ctl, int slots, hipStream_t st);
 hipError_t launch_met32_to_soa(const float* m32, const double* jac, double* dst, long long N, hipStream_t st);
 hipError_t launch_stats_accumulate(const double* q, double* acc, long long N, double gamma, hipStream_t st);
@@ -1153,7 +1153,7 @@ struct jz_batch {
   int cap;                 // member slots of the device tables
   int total;               // tiles of all members
   long long npoints;
-  bool half;               // every member has tv_alpha = 1/2: the stage kernels without pow
+  bool fast;               // every member allows the FAST stage kernels (fast_form)
   bool use_graph, graph_ok;
   hipGraph_t graph;
   hipGraphExec_t exec;
@@ -1269,15 +1269,15 @@ int batch_tables(jz_batch* b) {
   }
   b->total = off[n];
   fill_worklist(b->m, c);
-  // A member with another exponent moves the batch to the general kernels,
-  // which serve both, and a captured step with it (a new capture follows;
-  // the last use of the old one has to end first).
-  bool half = true;
-  for (jz_solver* s : b->m) half = half && s->ph.alpha_half;
-  if (b->half && !half) {
+  // A member that does not allow the FAST kernels moves the batch to the
+  // general ones, which serve every block, and a captured step with it (a new
+  // capture follows; the last use of the old one has to end first).
+  bool fast = true;
+  for (jz_solver* s : b->m) fast = fast && fast_form(s->ph, s->ni, s->nj);
+  if (b->fast && !fast) {
     if (b->graph_ok) HIP_TRY(hipStreamSynchronize(b->st));
     batch_drop_graph(b);
-    b->half = false;
+    b->fast = false;
   }
   if (n > 0) HIP_TRY(hipMemcpyAsync(b->d_desc, d, n * sizeof(BlockDesc), hipMemcpyHostToDevice, b->st));
   HIP_TRY(hipMemcpyAsync(b->d_off, off, (n + 1) * sizeof(int), hipMemcpyHostToDevice, b->st));
@@ -1363,10 +1363,10 @@ int batch_step_launches(jz_batch* b) {
   for (int k = 0; k < b->ns; ++k) {
     if (b->prec == JZ_FP64)
       HIP_TRY(launch_stage_batch_fp64(b->d_desc, b->d_off, b->d_ctl, k, b->ns, b->alpha[k], b->bx, b->by,
-                                      b->half, b->st));
+                                      b->fast, b->st));
     else
       HIP_TRY(launch_stage_batch_fp32(b->d_desc, b->d_off, b->d_ctl, k, b->ns, b->alpha[k], b->bx, b->by,
-                                      b->half, b->st));
+                                      b->fast, b->st));
   }
   HIP_TRY(launch_finalize_batch(b->d_desc, b->d_ctl, b->cap, b->st));
   return JZ_OK;
@@ -1423,7 +1423,7 @@ int jz_batch_create(jz_solver* const* members, int nmembers, void* hip_stream, j
   b->stage_bytes = 0;
   b->stage_next = 0;
   b->ev_member = nullptr;
-  b->half = true;
+  b->fast = true;
   b->use_graph = true;
   b->graph_ok = false;
   b->graph = nullptr;
@@ -2143,7 +2143,7 @@ int jz_domain_advance(jz_domain* D, int nsteps) {
         // one persistent launch over the tiles of every part
         const double alpha = D->p.rk_alpha[k];
         HIP_TRY(launch_stage_batch_fp64(D->d_desc, D->d_off, D->d_ctl, k, ns, alpha, D->bx, D->by,
-                                        D->p.tv_alpha == 0.5, D->stream));
+                                        fast_form(D->sub[0]->ph, D->n[0] + 4, D->n[1]), D->stream));
       } else {
         for (jz_solver* s : D->sub) {
           const void* in = k == 0 ? (const void*)s->q0 : dom_stage_out(s, k - 1, ns);

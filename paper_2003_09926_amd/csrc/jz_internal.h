@@ -22,6 +22,13 @@ struct Phys {
   int pad;
 };
 
+// Whether a block runs the FAST instantiations of the kernels: the exponent
+// 1/2 (no pow) and planes whose byte offsets fit 32 bits in every array (the
+// widest record is 80 bytes a node).
+inline bool fast_form(const Phys& ph, int ni, int nj) {
+  return ph.alpha_half && (long long)ni * nj * 80 <= 0xffffffffLL;
+}
+
 // Device-resident clock and diagnostics of one solver (lives in the workspace).
 struct Clock {
   double t;          // simulated time

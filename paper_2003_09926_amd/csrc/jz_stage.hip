@@ -4,24 +4,24 @@
 
 namespace jz {
 
-template <int BX, int BY, bool HALF>
+template <int BX, int BY, bool FAST>
 static hipError_t launch_shape64_as(const StageArgs& a, const int* flag, int mode, int nblocks, hipStream_t st) {
   const dim3 grid(nblocks), block(stage_threads<double, BX, BY>());
   switch (mode) {
-    case 0: hipLaunchKernelGGL((stage_kernel<double, double, double, false, BX, BY, 0, HALF>), grid, block, 0, st, a, flag); break;
-    case 1: hipLaunchKernelGGL((stage_kernel<double, double, double, false, BX, BY, 1, HALF>), grid, block, 0, st, a, flag); break;
-    case 2: hipLaunchKernelGGL((stage_kernel<double, double, double, false, BX, BY, 2, HALF>), grid, block, 0, st, a, flag); break;
-    case 3: hipLaunchKernelGGL((stage_kernel<double, double, double, false, BX, BY, 3, HALF>), grid, block, 0, st, a, flag); break;
-    case 4: hipLaunchKernelGGL((stage_kernel<double, double, double, false, BX, BY, 4, HALF>), grid, block, 0, st, a, flag); break;
+    case 0: hipLaunchKernelGGL((stage_kernel<double, double, double, false, BX, BY, 0, FAST>), grid, block, 0, st, a, flag); break;
+    case 1: hipLaunchKernelGGL((stage_kernel<double, double, double, false, BX, BY, 1, FAST>), grid, block, 0, st, a, flag); break;
+    case 2: hipLaunchKernelGGL((stage_kernel<double, double, double, false, BX, BY, 2, FAST>), grid, block, 0, st, a, flag); break;
+    case 3: hipLaunchKernelGGL((stage_kernel<double, double, double, false, BX, BY, 3, FAST>), grid, block, 0, st, a, flag); break;
+    case 4: hipLaunchKernelGGL((stage_kernel<double, double, double, false, BX, BY, 4, FAST>), grid, block, 0, st, a, flag); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
-// tv_alpha = 1/2, or any other exponent (see node_scales)
+// the FAST instantiation where the block allows it (see fast_form)
 template <int BX, int BY>
 static hipError_t launch_shape64(const StageArgs& a, const int* flag, int mode, int nblocks, hipStream_t st) {
-  return a.ph.alpha_half ? launch_shape64_as<BX, BY, true>(a, flag, mode, nblocks, st)
+  return fast_form(a.ph, a.ni, a.nj) ? launch_shape64_as<BX, BY, true>(a, flag, mode, nblocks, st)
                          : launch_shape64_as<BX, BY, false>(a, flag, mode, nblocks, st);
 }
 
@@ -75,10 +75,10 @@ int stage_wg_per_cu_fp64(int bx, int by) {
 // ---------------------------------------------------------------------------
 // persistent batch launches (FP64)
 // ---------------------------------------------------------------------------
-template <int BX, int BY, int MODE, bool HALF>
+template <int BX, int BY, int MODE, bool FAST>
 static hipError_t batch_one64(const BlockDesc* d, const int* off, BatchCtl* ctl, int stage, int ns, double alpha,
                               hipStream_t st) {
-  auto kern = stage_batch_kernel<double, double, double, false, BX, BY, MODE, HALF>;
+  auto kern = stage_batch_kernel<double, double, double, false, BX, BY, MODE, FAST>;
   int per_cu = 0, dev = 0, ncu = 0;
   hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, stage_threads<double, BX, BY>(), 0);
   if (e != hipSuccess) return e;
@@ -92,23 +92,23 @@ static hipError_t batch_one64(const BlockDesc* d, const int* off, BatchCtl* ctl,
   return hipGetLastError();
 }
 
-template <int BX, int BY, bool HALF>
+template <int BX, int BY, bool FAST>
 static hipError_t batch_shape64_as(const BlockDesc* d, const int* off, BatchCtl* ctl, int stage, int ns, double alpha,
                                 hipStream_t st) {
   const int mode = (stage == 0 ? 1 : 0) | (stage == ns - 1 ? 2 : 0);
   switch (mode) {
-    case 0: return batch_one64<BX, BY, 0, HALF>(d, off, ctl, stage, ns, alpha, st);
-    case 1: return batch_one64<BX, BY, 1, HALF>(d, off, ctl, stage, ns, alpha, st);
-    case 2: return batch_one64<BX, BY, 2, HALF>(d, off, ctl, stage, ns, alpha, st);
+    case 0: return batch_one64<BX, BY, 0, FAST>(d, off, ctl, stage, ns, alpha, st);
+    case 1: return batch_one64<BX, BY, 1, FAST>(d, off, ctl, stage, ns, alpha, st);
+    case 2: return batch_one64<BX, BY, 2, FAST>(d, off, ctl, stage, ns, alpha, st);
     default: return hipErrorInvalidValue;  // batches take at least two stages
   }
 }
 
-// half: every member has tv_alpha = 1/2 (otherwise the general kernel serves all of them)
+// fast: every member allows the FAST instantiation (otherwise the general one serves all of them)
 template <int BX, int BY>
 static hipError_t batch_shape64(const BlockDesc* d, const int* off, BatchCtl* ctl, int stage, int ns, double alpha,
-                                bool half, hipStream_t st) {
-  return half ? batch_shape64_as<BX, BY, true>(d, off, ctl, stage, ns, alpha, st)
+                                bool fast, hipStream_t st) {
+  return fast ? batch_shape64_as<BX, BY, true>(d, off, ctl, stage, ns, alpha, st)
               : batch_shape64_as<BX, BY, false>(d, off, ctl, stage, ns, alpha, st);
 }
 
@@ -118,12 +118,12 @@ bool batch64_shape_supported(int bx, int by) {
 }
 
 hipError_t launch_stage_batch_fp64(const BlockDesc* d, const int* off, BatchCtl* ctl, int stage, int ns, double alpha,
-                                   int bx, int by, bool half, hipStream_t st) {
-  if (bx == 32 && by == 16) return batch_shape64<32, 16>(d, off, ctl, stage, ns, alpha, half, st);
-  if (bx == 16 && by == 16) return batch_shape64<16, 16>(d, off, ctl, stage, ns, alpha, half, st);
-  if (bx == 36 && by == 12) return batch_shape64<36, 12>(d, off, ctl, stage, ns, alpha, half, st);
-  if (bx == 20 && by == 20) return batch_shape64<20, 20>(d, off, ctl, stage, ns, alpha, half, st);
-  if (bx == 20 && by == 16) return batch_shape64<20, 16>(d, off, ctl, stage, ns, alpha, half, st);
+                                   int bx, int by, bool fast, hipStream_t st) {
+  if (bx == 32 && by == 16) return batch_shape64<32, 16>(d, off, ctl, stage, ns, alpha, fast, st);
+  if (bx == 16 && by == 16) return batch_shape64<16, 16>(d, off, ctl, stage, ns, alpha, fast, st);
+  if (bx == 36 && by == 12) return batch_shape64<36, 12>(d, off, ctl, stage, ns, alpha, fast, st);
+  if (bx == 20 && by == 20) return batch_shape64<20, 20>(d, off, ctl, stage, ns, alpha, fast, st);
+  if (bx == 20 && by == 16) return batch_shape64<20, 16>(d, off, ctl, stage, ns, alpha, fast, st);
   return hipErrorInvalidValue;
 }
 

@@ -15,30 +15,30 @@ namespace jz {
 //       2 = last stage (float in, double out, next-dt lambda)
 //       3 = single stage (double in, double out, norms + lambda)
 //       4 = residual evaluation (double in, double R out)
-template <int BX, int BY, bool HALF>
+template <int BX, int BY, bool FAST>
 static hipError_t launch_shape32_as(const StageArgs& a, const int* flag, int kind, int nblocks, hipStream_t st) {
   const dim3 grid(nblocks), block(stage_threads<float, BX, BY>());
   switch (kind) {
     case 0:
-      if (a.ref) hipLaunchKernelGGL((stage_kernel<float, double, float, true, BX, BY, 9, HALF>), grid, block, 0, st, a, flag);
-      else hipLaunchKernelGGL((stage_kernel<float, double, float, true, BX, BY, 1, HALF>), grid, block, 0, st, a, flag);
+      if (a.ref) hipLaunchKernelGGL((stage_kernel<float, double, float, true, BX, BY, 9, FAST>), grid, block, 0, st, a, flag);
+      else hipLaunchKernelGGL((stage_kernel<float, double, float, true, BX, BY, 1, FAST>), grid, block, 0, st, a, flag);
       break;
     case 1:
-      if (a.ref) hipLaunchKernelGGL((stage_kernel<float, float, float, true, BX, BY, 8, HALF>), grid, block, 0, st, a, flag);
-      else hipLaunchKernelGGL((stage_kernel<float, float, float, true, BX, BY, 0, HALF>), grid, block, 0, st, a, flag);
+      if (a.ref) hipLaunchKernelGGL((stage_kernel<float, float, float, true, BX, BY, 8, FAST>), grid, block, 0, st, a, flag);
+      else hipLaunchKernelGGL((stage_kernel<float, float, float, true, BX, BY, 0, FAST>), grid, block, 0, st, a, flag);
       break;
-    case 2: hipLaunchKernelGGL((stage_kernel<float, float, double, true, BX, BY, 2, HALF>), grid, block, 0, st, a, flag); break;
-    case 3: hipLaunchKernelGGL((stage_kernel<float, double, double, true, BX, BY, 3, HALF>), grid, block, 0, st, a, flag); break;
-    case 4: hipLaunchKernelGGL((stage_kernel<float, double, double, true, BX, BY, 4, HALF>), grid, block, 0, st, a, flag); break;
+    case 2: hipLaunchKernelGGL((stage_kernel<float, float, double, true, BX, BY, 2, FAST>), grid, block, 0, st, a, flag); break;
+    case 3: hipLaunchKernelGGL((stage_kernel<float, double, double, true, BX, BY, 3, FAST>), grid, block, 0, st, a, flag); break;
+    case 4: hipLaunchKernelGGL((stage_kernel<float, double, double, true, BX, BY, 4, FAST>), grid, block, 0, st, a, flag); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
-// tv_alpha = 1/2, or any other exponent (see node_scales)
+// the FAST instantiation where the block allows it (see fast_form)
 template <int BX, int BY>
 static hipError_t launch_shape32(const StageArgs& a, const int* flag, int kind, int nblocks, hipStream_t st) {
-  return a.ph.alpha_half ? launch_shape32_as<BX, BY, true>(a, flag, kind, nblocks, st)
+  return fast_form(a.ph, a.ni, a.nj) ? launch_shape32_as<BX, BY, true>(a, flag, kind, nblocks, st)
                          : launch_shape32_as<BX, BY, false>(a, flag, kind, nblocks, st);
 }
 
@@ -74,10 +74,10 @@ int stage_wg_per_cu_fp32(int bx, int by) {
 // ---------------------------------------------------------------------------
 // persistent batch launches (FP32-flux)
 // ---------------------------------------------------------------------------
-template <typename TIn, typename TOut, int BX, int BY, int MODE, bool HALF>
+template <typename TIn, typename TOut, int BX, int BY, int MODE, bool FAST>
 static hipError_t batch_one32(const BlockDesc* d, const int* off, BatchCtl* ctl, int stage, int ns, double alpha,
                               hipStream_t st) {
-  auto kern = stage_batch_kernel<float, TIn, TOut, true, BX, BY, MODE, HALF>;
+  auto kern = stage_batch_kernel<float, TIn, TOut, true, BX, BY, MODE, FAST>;
   int per_cu = 0, dev = 0, ncu = 0;
   hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, stage_threads<float, BX, BY>(), 0);
   if (e != hipSuccess) return e;
@@ -91,19 +91,19 @@ static hipError_t batch_one32(const BlockDesc* d, const int* off, BatchCtl* ctl,
   return hipGetLastError();
 }
 
-template <int BX, int BY, bool HALF>
+template <int BX, int BY, bool FAST>
 static hipError_t batch_shape32_as(const BlockDesc* d, const int* off, BatchCtl* ctl, int stage, int ns, double alpha,
                                 hipStream_t st) {
-  if (stage == 0) return batch_one32<double, float, BX, BY, 1, HALF>(d, off, ctl, stage, ns, alpha, st);
-  if (stage == ns - 1) return batch_one32<float, double, BX, BY, 2, HALF>(d, off, ctl, stage, ns, alpha, st);
-  return batch_one32<float, float, BX, BY, 0, HALF>(d, off, ctl, stage, ns, alpha, st);
+  if (stage == 0) return batch_one32<double, float, BX, BY, 1, FAST>(d, off, ctl, stage, ns, alpha, st);
+  if (stage == ns - 1) return batch_one32<float, double, BX, BY, 2, FAST>(d, off, ctl, stage, ns, alpha, st);
+  return batch_one32<float, float, BX, BY, 0, FAST>(d, off, ctl, stage, ns, alpha, st);
 }
 
-// half: every member has tv_alpha = 1/2 (otherwise the general kernel serves all of them)
+// fast: every member allows the FAST instantiation (otherwise the general one serves all of them)
 template <int BX, int BY>
 static hipError_t batch_shape32(const BlockDesc* d, const int* off, BatchCtl* ctl, int stage, int ns, double alpha,
-                                bool half, hipStream_t st) {
-  return half ? batch_shape32_as<BX, BY, true>(d, off, ctl, stage, ns, alpha, st)
+                                bool fast, hipStream_t st) {
+  return fast ? batch_shape32_as<BX, BY, true>(d, off, ctl, stage, ns, alpha, st)
               : batch_shape32_as<BX, BY, false>(d, off, ctl, stage, ns, alpha, st);
 }
 
@@ -112,11 +112,11 @@ bool batch32_shape_supported(int bx, int by) {
 }
 
 hipError_t launch_stage_batch_fp32(const BlockDesc* d, const int* off, BatchCtl* ctl, int stage, int ns, double alpha,
-                                   int bx, int by, bool half, hipStream_t st) {
-  if (bx == 32 && by == 24) return batch_shape32<32, 24>(d, off, ctl, stage, ns, alpha, half, st);
-  if (bx == 32 && by == 16) return batch_shape32<32, 16>(d, off, ctl, stage, ns, alpha, half, st);
-  if (bx == 16 && by == 16) return batch_shape32<16, 16>(d, off, ctl, stage, ns, alpha, half, st);
-  if (bx == 36 && by == 20) return batch_shape32<36, 20>(d, off, ctl, stage, ns, alpha, half, st);
+                                   int bx, int by, bool fast, hipStream_t st) {
+  if (bx == 32 && by == 24) return batch_shape32<32, 24>(d, off, ctl, stage, ns, alpha, fast, st);
+  if (bx == 32 && by == 16) return batch_shape32<32, 16>(d, off, ctl, stage, ns, alpha, fast, st);
+  if (bx == 16 && by == 16) return batch_shape32<16, 16>(d, off, ctl, stage, ns, alpha, fast, st);
+  if (bx == 36 && by == 20) return batch_shape32<36, 20>(d, off, ctl, stage, ns, alpha, fast, st);
   return hipErrorInvalidValue;
 }
 

@@ -216,8 +216,10 @@ constexpr int lds_pitch() {
 // One tile (logical index lt of the block described by A) through one stage.
 // Partial norms and lambda maxima go to slot lt, so the reductions do not
 // depend on how tiles are scheduled.  Every thread of the workgroup calls it;
+// FAST: exponent 1/2 and 32-bit column offsets (fast_form); the general
+// instantiation takes any block, with the same results.
 // PERSIST: called from the persistent batch kernel's tile loop.
-template <typename Rl, typename TIn, typename TOut, bool MET32, int BX, int BY, int MODE, bool HALF, bool PERSIST>
+template <typename Rl, typename TIn, typename TOut, bool MET32, int BX, int BY, int MODE, bool FAST, bool PERSIST>
 __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
   constexpr int NT = stage_threads<Rl, BX, BY>();  // threads of the workgroup
   constexpr int TI = BX - 4, TJ = BY - 4;
@@ -330,14 +332,21 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
   const int c = tx + P * ty;                      // LDS slot of this column
   const int ui = i0 - 2 + tx, uj = j0 - 2 + ty;  // unwrapped column indices
   const bool bi = A.in.bnd & 1, bj = A.in.bnd & 2, bk = A.in.bnd & 4;
-  const long long col = (long long)map_index(ui, A.ni, bi) + (long long)A.ni * map_index(uj, A.nj, bj);
+  // Addresses are a base per plane (uniform: scalar registers and arithmetic)
+  // plus the byte offset of the column in its plane, 32 bits wide in the FAST
+  // instantiations (planes of less than 4 GiB in every array), and the mapped
+  // plane indices step along instead of being reduced modulo nk each time: one
+  // 64-bit add per array and plane (80 scalar and 36 vector instructions less
+  // per FP64 plane; step at 512 x 256 x 256: FP64 8.74 -> 8.68 ms, FP32-flux,
+  // which is bound by instruction issue, 4.74 -> 4.58 ms).
+  typedef typename std::conditional<FAST, uint32_t, uint64_t>::type Off;
+  const Off col = (Off)map_index(ui, A.ni, bi) + (Off)A.ni * (Off)map_index(uj, A.nj, bj);
   const long long plane = (long long)A.ni * A.nj;
   // compact form: the second-ring column an edge thread supplies (slot cB)
   const bool hasB = COMPACT && role == 1;
   const int cB = tx2 + P * ty2;
-  const long long colB = COMPACT ? (long long)map_index(i0 - 2 + tx2, A.ni, bi) +
-                                       (long long)A.ni * map_index(j0 - 2 + ty2, A.nj, bj)
-                                 : 0;
+  const Off colB = COMPACT ? (Off)map_index(i0 - 2 + tx2, A.ni, bi) + (Off)A.ni * (Off)map_index(j0 - 2 + ty2, A.nj, bj)
+                           : 0;
   // supplies primitives and Q.  In the compact form the four idle threads
   // do too, for the never-read second-ring corner slot (0, 0): then every
   // lane issues the same prefetch loads (see below).
@@ -349,17 +358,34 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
   const int ch = HELP ? (2 + hl % TI) + P * (2 + hl / TI) : 0;
   const bool isH = HELP && t >= NI && t < 2 * NI && (i0 + hl % TI) < A.in.hi[0] && (j0 + hl / TI) < A.in.hi[1];
 
-  const TIn* __restrict__ qin = (const TIn*)A.qin;
-  TOut* __restrict__ qout = (TOut*)A.qout;
-  MetView<MET32> met;
-  met.m = (decltype(met.m))A.met;
-  met.jac = A.jac;
   const double dt = A.clock->dt;
   const double adt = A.alpha * dt;
   const bool q0_is_input = (const void*)A.qin == (const void*)A.q0;
 
-  auto node = [&](int k) { return col + plane * map_index(k, A.nk, bk); };
-  auto nodeB = [&](int k) { return colB + plane * map_index(k, A.nk, bk); };
+  // mapped plane index of k, and of the plane after mapped plane k.  (The
+  // planes a chunk of a bounded direction reads all lie in the block: its
+  // boundary layers are two planes deep.)
+  auto kmap = [&](int k) { return map_index(k, A.nk, bk); };
+  auto knext = [&](int k) { return k + 1 == A.nk ? 0 : k + 1; };
+  // C values of type T per node: the five of this column's node in mapped plane k
+  auto at = [&](auto* base, int C, int k) {
+    typedef typename std::remove_pointer<decltype(base)>::type T;
+    typedef typename std::conditional<std::is_const<T>::value, const char, char>::type Byte;
+    return (T*)((Byte*)(base + (long long)C * plane * k) + (Off)(col * (Off)(C * sizeof(T))));
+  };
+  auto load_q = [&](int k, Rl q[5]) {
+    const TIn* w = at((const TIn*)A.qin, 5, k);
+#pragma unroll
+    for (int v = 0; v < 5; ++v) q[v] = (Rl)w[v];
+  };
+  auto load_met = [&](int k, auto sm[9], double& J) {
+    typedef typename std::conditional<MET32, float, double>::type MS;
+    const MS* w = at((const MS*)A.met, MET32 ? 9 : 10, k);
+#pragma unroll
+    for (int v = 0; v < 9; ++v) sm[v] = w[v];
+    if constexpr (MET32) J = *at(A.jac, 1, k);
+    else J = w[9];
+  };
   typedef __attribute__((address_space(3))) uint32_t* lds_u32;
   // the ten 4-byte words of the five doubles at src, lane by lane, into rows
   // of `pitch` words starting at LDS byte address base (uniform per wave)
@@ -383,10 +409,11 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
     }
   };
   // Q of plane k of an edge thread's second-ring column into sQB
-  auto qb_fetch = [&](int k) {
-    if constexpr (COMPACT)
-      dma_q(reinterpret_cast<const double*>(qin) + 5 * nodeB(k),
+  auto qb_fetch = [&](int k) {  // k: mapped plane
+    if constexpr (COMPACT) {
+      dma_q((const double*)((const char*)((const double*)A.qin + 5 * plane * k) + (Off)(colB * (Off)40)),
             __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_u32)&sQB[0][0]), 64);
+    }
   };
   const int laneB = t - NI;   // an edge thread's column in sQB
   // primitives u, v, w, T, p of a column's Q, in the order of the sPr rows
@@ -425,15 +452,13 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
   Rl PrM[5] = {0, 0, 0, 0, 0}, PrC[5] = {0, 0, 0, 0, 0};
 #pragma unroll
   for (int v = 0; v < 5; ++v) Qs[v] = Qg[v] = Qn[v] = Qm[v] = 0;
+  // mapped planes: s (updated), s + 2 (metric prefetch), s + 3 (lead prefetch)
+  int ks = kmap(kbeg - 2), km = kmap(kbeg - 1), kl = kmap(kbeg);
   if (isP) {
-    const long long n0 = node(kbeg - 2), n1 = node(kbeg - 1), n2 = node(kbeg);
-#pragma unroll
-    for (int v = 0; v < 5; ++v) {
-      Qs[v] = (Rl)qin[5 * n0 + v];
-      Qg[v] = (Rl)qin[5 * n1 + v];
-      Qn[v] = (Rl)qin[5 * n2 + v];
-    }
-    if (COMPACT || isG) met.load(n1, Mn, MJn);
+    load_q(ks, Qs);
+    load_q(km, Qg);
+    load_q(kl, Qn);
+    if (COMPACT || isG) load_met(km, Mn, MJn);
     prims_of(Qs, PrM);
     prims_of(Qg, PrC);
     if constexpr (!ZREG) {
@@ -442,7 +467,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
     }
   }
   // the second-ring column's first gradient plane
-  if (hasB) qb_fetch(kbeg - 1);
+  if (hasB) qb_fetch(km);
 
   for (int s = kbeg - 2; s < kend; ++s) {
     // ---- lead plane s+2 (prefetched); prefetch plane s+3 -------------------
@@ -462,11 +487,8 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
     // chunk, reloads the last plane it needs: the same loads on every path
     // let the compiler count them when it waits for older loads, instead of
     // assuming they were skipped and waiting for everything in flight.
-    if (isP && (COMPACT || s + 3 < kend + 2)) {
-      const long long nn = node(COMPACT ? min(s + 3, kend + 1) : s + 3);
-#pragma unroll
-      for (int v = 0; v < 5; ++v) Qn[v] = (Rl)qin[5 * nn + v];
-    }
+    if (s + 3 < kend + 2) kl = knext(kl);
+    if (isP && (COMPACT || s + 3 < kend + 2)) load_q(kl, Qn);
     // No barrier here: the primitive plane written now (slot_l; the single
     // plane when ZREG) was last read in the previous step's gradient phase
     // (before its second barrier).  The Q, flux, scale and sensor buffers are
@@ -508,7 +530,6 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
     // stages of the compact form issue these loads as soon as the flux
     // contraction has freed its registers, the other stages and shapes (whose
     // registers do not allow that) just before the second barrier
-    const long long ns = node(s);
     constexpr bool Q0_IN_REGS = std::is_same<Rl, double>::value && std::is_same<TIn, double>::value;
     double q0v[5] = {0, 0, 0, 0, 0};
     MT mo[9];
@@ -517,18 +538,19 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
     auto update_loads = [&]() {
       if (!(Q0_IN_REGS && q0_is_input)) {
 #pragma unroll
-        for (int v = 0; v < 5; ++v) q0v[v] = A.q0[5 * ns + v];
+        for (int v = 0; v < 5; ++v) q0v[v] = at(A.q0, 5, ks)[v];
       }
-      if (LAMMAX && !MET_LDS) met.load(ns, mo, moJ);
+      if (LAMMAX && !MET_LDS) load_met(ks, mo, moJ);
     };
+    if (s + 2 < kend + 1) km = knext(km);
     Rl m[9];
     if constexpr (COMPACT) {
 #pragma unroll
       for (int k = 0; k < 9; ++k) m[k] = move_apart(Mn[k]);
       Jg = move_apart(MJn);
-      met.load(node(min(s + 2, kend)), Mn, MJn);
+      load_met(km, Mn, MJn);
       // the second-ring column's next gradient plane, straight into LDS
-      if (hasB && s + 1 < kend) qb_fetch(s + 2);
+      if (hasB && s + 1 < kend) qb_fetch(km);
     }
     if (isG) {
       if constexpr (!COMPACT) {
@@ -540,7 +562,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
           for (int k = 0; k < 9; ++k) sMo[(s + 1) & 1][k][t] = (MT)m[k];
           sMoJ[(s + 1) & 1][t] = Jg;
         }
-        if (s + 2 < kend + 1) met.load(node(s + 2), Mn, MJn);
+        if (s + 2 < kend + 1) load_met(km, Mn, MJn);
       }
       const Rl(*Pg)[NS] = sPr[ZREG ? 0 : slot_g];
       // Every primitive this column needs from the three planes, read in one
@@ -576,7 +598,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
         if (upd) update_loads();
       }
       Rl sig[3];
-      node_scales<HALF>(ph, m, Uc, asnd, sig);
+      node_scales<FAST>(ph, m, Uc, asnd, sig);
       sSx[c] = sig[0];
       sSy[c] = sig[1];
       sigg = sig[2];
@@ -671,7 +693,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
         for (int v = 0; v < 5; ++v) R[v] = Js * (double)(Acc[v] + Hp[v]);
         if (WRITE_R) {
 #pragma unroll
-          for (int v = 0; v < 5; ++v) qout[5 * ns + v] = (TOut)R[v];
+          for (int v = 0; v < 5; ++v) at((TOut*)A.qout, 5, ks)[v] = (TOut)R[v];
         } else {
           double qn[5];
           // In the first stage the stencil input is Q(0) itself and, in the
@@ -684,7 +706,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
             for (int v = 0; v < 5; ++v) qn[v] = q0v[v] - adt * R[v];
           }
 #pragma unroll
-          for (int v = 0; v < 5; ++v) qout[5 * ns + v] = (TOut)qn[v];
+          for (int v = 0; v < 5; ++v) at((TOut*)A.qout, 5, ks)[v] = (TOut)qn[v];
           if constexpr (KEEP_REF) {
             // a node on a far-field reference plane also keeps its double
             // update (see StageArgs::ref)
@@ -751,6 +773,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
     nus = nug;
     sigs = sigg;
     Js = Jg;
+    ks = knext(ks);
     const int old_s = slot_s;
     slot_s = slot_g;
     slot_g = slot_l;
@@ -811,11 +834,11 @@ constexpr int stage_waves_per_eu() {
 }
 
 // Single block: one workgroup per tile, tiles spread XCD by XCD.
-template <typename Rl, typename TIn, typename TOut, bool MET32, int BX, int BY, int MODE, bool HALF>
+template <typename Rl, typename TIn, typename TOut, bool MET32, int BX, int BY, int MODE, bool FAST>
 __global__ __launch_bounds__((stage_threads<Rl, BX, BY>()))
 __attribute__((amdgpu_waves_per_eu(stage_waves_per_eu<Rl, BX, BY, MODE>()))) void stage_kernel(StageArgs A, const int* __restrict__ flag) {
   if (*flag) return;  // a failed step froze the state
-  stage_tile<Rl, TIn, TOut, MET32, BX, BY, MODE, HALF, false>(A, xcd_remap(blockIdx.x, gridDim.x));
+  stage_tile<Rl, TIn, TOut, MET32, BX, BY, MODE, FAST, false>(A, xcd_remap(blockIdx.x, gridDim.x));
 }
 
 // Many blocks in one persistent launch.  The tiles of all blocks form one
@@ -826,7 +849,7 @@ __attribute__((amdgpu_waves_per_eu(stage_waves_per_eu<Rl, BX, BY, MODE>()))) voi
 // the slot's counter, so a workgroup that drew short tiles takes more of
 // them, and every workgroup exits once its slot's share is claimed.  The
 // grid is at least kBatchSlots workgroups, so every slot is served.
-template <typename Rl, typename TIn, typename TOut, bool MET32, int BX, int BY, int MODE, bool HALF>
+template <typename Rl, typename TIn, typename TOut, bool MET32, int BX, int BY, int MODE, bool FAST>
 __global__ __launch_bounds__((stage_threads<Rl, BX, BY>()))
 __attribute__((amdgpu_waves_per_eu(stage_waves_per_eu<Rl, BX, BY, MODE>()))) void stage_batch_kernel(const BlockDesc* __restrict__ desc,
                                                              const int* __restrict__ tile_off,
@@ -873,7 +896,7 @@ __attribute__((amdgpu_waves_per_eu(stage_waves_per_eu<Rl, BX, BY, MODE>()))) voi
     A.nchunks = D.nchunks;
     A.in = D.in;
     A.ph = D.ph;
-    stage_tile<Rl, TIn, TOut, MET32, BX, BY, MODE, HALF, true>(A, g - tile_off[a]);
+    stage_tile<Rl, TIn, TOut, MET32, BX, BY, MODE, FAST, true>(A, g - tile_off[a]);
   }
 }
 
