@@ -258,10 +258,11 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
   // every thread has finished reading the previous plane's Q); the other
   // shapes write before that barrier, alternating between two buffers.
   constexpr int NQB = COMPACT ? 1 : 2;
-  __shared__ Rl sQ2[NQB][5][NS];
-  __shared__ __attribute__((aligned(16))) Rl sF[10][NS];  // Fhat^xi (rows 0-4), Fhat^eta (rows 5-9)
-  Rl(*sFx)[NS] = sF;
-  Rl(*sFy)[NS] = sF + 5;
+  // One array with the fluxes, so that a single base register per variable
+  // reaches the variable's Q and both its fluxes at immediate offsets.
+  __shared__ __attribute__((aligned(16))) Rl sQF[5 * NQB + 10][NS];  // Q, Fhat^xi, Fhat^eta (5 rows each)
+  Rl(*sFx)[NS] = sQF + 5 * NQB;
+  Rl(*sFy)[NS] = sFx + 5;
   __shared__ Rl sSx[NS], sSy[NS];  // sigma^xi, sigma^eta
   __shared__ Rl sNx[NS], sNy[NS];  // pressure sensor along xi, eta
   // helpers' in-plane terms of variables NV_OWN..4 of the owned columns, by march-step parity
@@ -296,7 +297,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
   __shared__ uint32_t sQB[COMPACT ? 10 : 1][COMPACT ? 64 : 1];
   // end-of-tile reductions reuse the flux buffer (free once the march is done)
   static_assert(sizeof(Rl) * 10 * NS >= sizeof(double) * 2 * NT, "reduction rows exceed the flux buffer");
-  double(*sRed)[NT] = reinterpret_cast<double(*)[NT]>(&sF[0][0]);
+  double(*sRed)[NT] = reinterpret_cast<double(*)[NT]>(&sFx[0][0]);
 
   const Phys ph = A.ph;
   const Rl gm1 = (Rl)ph.gm1, gamma = (Rl)ph.gamma;
@@ -469,7 +470,26 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
   // the second-ring column's first gradient plane
   if (hasB) qb_fetch(km);
 
-  for (int s = kbeg - 2; s < kend; ++s) {
+  // The rows of LDS that the unrolled in-plane trips read, each behind a base
+  // register of its own that the compiler cannot see through (every access is
+  // then base plus immediate offset), set once for the whole march.
+  constexpr int UNR = sizeof(Rl) == 8 ? 5 : 1;
+  constexpr bool ROW_BASES = COMPACT && UNR == 5;
+  typedef __attribute__((address_space(3))) const Rl* lds_ptr;
+  lds_ptr rowb[5];
+  if constexpr (ROW_BASES) {
+#pragma unroll
+    for (int v = 0; v < 5; ++v) {
+      rowb[v] = (lds_ptr)&sQF[v][c - 2 * P];
+      asm volatile("" : "+v"(rowb[v]));
+    }
+  }
+
+  // One march step.  The loop below holds several copies of it in the default
+  // shapes, so that the shift of the column registers by a plane at its end
+  // becomes mostly renaming: of the 50 register moves of an FP64 plane, 18
+  // are left with three copies.
+  auto march = [&](const int s) __attribute__((always_inline)) {
     // ---- lead plane s+2 (prefetched); prefetch plane s+3 -------------------
 #pragma unroll
     for (int v = 0; v < 5; ++v) Ql[v] = Qn[v];
@@ -494,7 +514,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
     // (before its second barrier).  The Q, flux, scale and sensor buffers are
     // rewritten only after the next barrier, which every thread reaches after
     // finishing the owned phase.
-    Rl(*sQ)[NS] = sQ2[NQB == 2 ? (s - kbeg) & 1 : 0];
+    Rl(*sQ)[NS] = sQF + (NQB == 2 ? 5 * ((s - kbeg) & 1) : 0);
     auto write_q = [&]() {
       if (isP) {
 #pragma unroll
@@ -507,7 +527,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
         for (int v = 0; v < 5; ++v) sQ[v][cB] = qb[v];
       }
     };
-    Rl PrL[5] = {0, 0, 0, 0, 0};  // primitives of the lead plane
+    Rl PrL[5];  // primitives of the lead plane
     if (isP) {
       prims_of(Ql, PrL);
       if constexpr (ZREG) write_prims(0, PrC);  // the gradient plane s+1
@@ -518,8 +538,10 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
     if constexpr (NQB == 1) write_q();
 
     // ---- gradient plane g = s+1: fluxes, dissipation scales, sensors ------
-    Rl Fzg[5] = {0, 0, 0, 0, 0}, sigg = 0, nug = 0;
-    double Jg = 0.0;
+    // (not initialised: lanes without fluxes never read theirs, and zeroing
+    // these and the like below cost an FP64 plane 28 register moves)
+    Rl Fzg[5], sigg, nug;
+    double Jg;
     // Take the prefetched metrics out of the prefetch registers (into other
     // registers: the early-clobber move keeps the two apart), so that the
     // prefetch for the next plane can land in place and is waited for only
@@ -531,9 +553,9 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
     // contraction has freed its registers, the other stages and shapes (whose
     // registers do not allow that) just before the second barrier
     constexpr bool Q0_IN_REGS = std::is_same<Rl, double>::value && std::is_same<TIn, double>::value;
-    double q0v[5] = {0, 0, 0, 0, 0};
+    double q0v[5];
     MT mo[9];
-    double moJ = 0.0;
+    double moJ;
     const bool upd = isI && s >= kbeg && !WRITE_R;  // plane s is updated in this step
     auto update_loads = [&]() {
       if (!(Q0_IN_REGS && q0_is_input)) {
@@ -613,7 +635,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
     // and s+1 needs only the column's registers (and the update loads start
     // here in the shapes other than the compact one)
     const bool own = isI && s >= kbeg - 1;  // plane kbeg-1 is not written
-    Rl Hp[5] = {0, 0, 0, 0, 0};
+    Rl Hp[5];
     if (own) {
       if constexpr (!(COMPACT && BASE == 0)) {
         if (upd) update_loads();
@@ -631,8 +653,6 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
     // are unrolled (the rotation becomes renaming).  FP32-flux: a rolled loop,
     // which measured faster there; it keeps no register indexed by the trip
     // count.
-    constexpr int UNR = sizeof(Rl) == 8 ? 5 : 1;
-    typedef __attribute__((address_space(3))) const Rl* lds_ptr;
     auto inplane = [&](int cc, int vb, int ve, Rl Rr[5]) {
       // xi faces cc-1/2 and cc+1/2, eta faces cc-P/2 and cc+P/2 (slots)
       Rl e2xp, e4xp, sgxp, e2xm, e4xm, sgxm, e2yp, e4yp, sgyp, e2ym, e4ym, sgym;
@@ -644,12 +664,19 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
       for (int v = vb; v < ve; ++v) {
         // The empty asm hides the array base, so that every neighbour
         // access is one base register plus an immediate offset.
-        lds_ptr q = (lds_ptr)&sQ[v][cc - 2 * P];
-        asm volatile("" : "+v"(q));
-        lds_ptr fx = (lds_ptr)&sFx[v][cc - 1];
-        asm volatile("" : "+v"(fx));
-        lds_ptr fy = (lds_ptr)&sFy[v][cc - P];
-        asm volatile("" : "+v"(fy));
+        lds_ptr q, fx, fy;
+        if constexpr (ROW_BASES) {
+          q = rowb[v];
+          fx = q + (5 * NS + 2 * P - 1);
+          fy = q + (10 * NS + P);
+        } else {
+          q = (lds_ptr)&sQ[v][cc - 2 * P];
+          asm volatile("" : "+v"(q));
+          fx = (lds_ptr)&sFx[v][cc - 1];
+          asm volatile("" : "+v"(fx));
+          fy = (lds_ptr)&sFy[v][cc - P];
+          asm volatile("" : "+v"(fy));
+        }
         const Rl q0 = q[2 * P];
         const Rl qxp = q[2 * P + 1], qxpp = q[2 * P + 2], qxm = q[2 * P - 1], qxmm = q[2 * P - 2];
         const Rl qyp = q[3 * P], qypp = q[4 * P], qym = q[P], qymm = q[0];
@@ -670,7 +697,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
     // (written one step earlier: the terms of its plane s)
     const int hbuf = (s - kbeg) & 1;
     if (HELP && isH && s >= kbeg - 1) {
-      Rl Rh[5] = {0, 0, 0, 0, 0};
+      Rl Rh[5];
       inplane(ch, NV_OWN, 5, Rh);
 #pragma unroll
       for (int k = 0; k < NHV; ++k) sRg[hbuf][k][ch] = Rh[5 - NHV + k];
@@ -748,7 +775,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
     };
     if (own) {
       if constexpr (UPDATE_FIRST) update();
-      Rl Rg[5] = {0, 0, 0, 0, 0};
+      Rl Rg[5];
       inplane(c, 0, NV_OWN, Rg);
       // the owner's variables sit in Rg[NHV..4]
       if (HELP) {
@@ -782,6 +809,21 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
     for (int k = 0; k < 5; ++k) {
       PrM[k] = PrC[k];
       PrC[k] = PrL[k];
+    }
+    };
+  // Copies per loop trip, measured at 512 x 256 x 256: FP64 compact form 8.75
+  // (one) / 8.70 (two) / 8.51 ms a step (three); FP32-flux 32 x 16 tiles 4.59 /
+  // 4.56 / 4.60 ms.
+  constexpr int COPIES = !FAST ? 1 : COMPACT ? 3 : (sizeof(Rl) == 4 && BX == 36) ? 2 : 1;
+  for (int s = kbeg - 2; s < kend; s += COPIES) {
+    march(s);
+    if constexpr (COPIES > 1) {
+      if (s + 1 >= kend) break;
+      march(s + 1);
+    }
+    if constexpr (COPIES > 2) {
+      if (s + 2 >= kend) break;
+      march(s + 2);
     }
   }
 
