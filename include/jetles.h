@@ -102,7 +102,9 @@ typedef struct {
   int n_stages;        /* 1..5 (5); with one stage (forward Euler) the stage writes a
                           stage buffer that is then copied into the state */
   int precision;       /* jz_precision (JZ_FP64) */
-  int tile_i, tile_j;  /* launch shape of the stage kernel; 0 = library default */
+  int tile_i, tile_j;  /* launch shape of the stage kernel; 0 = library default (with kchunk = 0
+                          too, a small block advances in bricks instead of marching in tiles:
+                          same states, RMS norms summed in another order) */
   int kchunk;          /* planes marched per workgroup; 0 = chosen by the library for
                           the current device (fills the last round of workgroups) */
   int bc[6];           /* jz_bc of the faces xi-, xi+, eta-, eta+, zeta-, zeta+ (all periodic) */
@@ -242,7 +244,9 @@ int jz_destroy(jz_solver* s);
  * stage count and coefficients, and a tile shape with a batch kernel
  * (FP64: 16x12, 32x8, 16x16, 28x12, 12x12; FP32-flux: 32x16, 28x20, 28x12, 12x12), and must have their
  * grid and state set.  Each member's results are bitwise those of the member
- * advanced alone with the same tile shape.  Members need n_stages >= 2 (JZ_EINVAL
+ * advanced alone with the same tile shape (a small member whose launch shape
+ * is left to the library advances alone in bricks, and its RMS norms may then
+ * differ from the batch's in the last bits).  Members need n_stages >= 2 (JZ_EINVAL
  * otherwise).  The caller keeps ownership of the members, must not advance
  * them on their own while they belong to the batch, and must take a member
  * out (jz_batch_remove) or destroy the batch before destroying the member.

@@ -17,6 +17,8 @@ hipError_t launch_stage_fp64(const StageArgs& a, const int* flag, int mode, int 
                              hipStream_t st);
 hipError_t launch_stage_fp32(const StageArgs& a, const int* flag, int kind, int bx, int by, int nblocks,
                              hipStream_t st);
+hipError_t launch_brick(const StageArgs& a, bool f32, const int* flag, int stage, bool last, int nbricks,
+                        hipStream_t st);
 bool stage_shape_supported(int bx, int by);
 bool stage32_shape_supported(int bx, int by);
 bool batch64_shape_supported(int bx, int by);
@@ -214,9 +216,33 @@ void pick_tiling_for_device(int ni, int nj, int nk, const jz_params* p, Tiling* 
 // Tiles of the finest supported tiling (interior 12 x 4 tiles with 8-plane
 // chunks bounds every shape in either precision), so the partial-sum arrays
 // never need to grow when the tiling changes.
-int partial_capacity(int ni, int nj, int nk, const Tiling& t) {
+int partial_capacity(int ni, int nj, int nk, const Tiling& t, int nbricks) {
   const int fine = ((ni + 11) / 12) * ((nj + 3) / 4) * ((nk + 7) / 8);
-  return fine > t.nblocks ? fine : t.nblocks;
+  return std::max(std::max(fine, t.nblocks), nbricks);
+}
+
+// Bricks a block is advanced in when the launch shape is left to the library
+// (0: it marches, see jz_brick.hip).  The bricks take about as many rounds as
+// there are bricks per workgroup slot, the march of a block this small the
+// time of its ten or so planes in turn, whatever its size.  Measured stage
+// launches, bricks / march: FP64 45 bricks (24 x 20 x 18) 10.4 / 32.9 us, 672
+// (61 x 47 x 53) 24.6 / 31.9, 1280 (80 x 64 x 64) 41.0 / 32.9, so three rounds
+// of one brick per CU; FP32-flux (two bricks per CU) 45 bricks 8.7 / 38.4 us,
+// 1280 22.5 / 36.5, 2160 (96 x 96 x 60) 36.2 / 37.0, so four rounds.
+constexpr int kMaxBricks64 = 768, kMaxBricks32 = 2048;
+
+int brick_count(int ni, int nj, int nk, const jz_params* p, int n[2] = nullptr) {
+  if (p && (p->tile_i > 0 || p->kchunk > 0 || p->n_stages < 2 || p->tv_alpha != 0.5)) return 0;
+  const Interior in = interior_of(ni, nj, nk, p);
+  const long long bi = (in.hi[0] - in.lo[0] + kBrickI - 1) / kBrickI, bj = (in.hi[1] - in.lo[1] + kBrickJ - 1) / kBrickJ,
+                  bk = (in.hi[2] - in.lo[2] + kBrickK - 1) / kBrickK;
+  const long long most = p && p->precision == JZ_FP32_FLUX ? kMaxBricks32 : kMaxBricks64;
+  if (bi > most || bj > most || bk > most || bi * bj * bk > most) return 0;
+  if (n) {
+    n[0] = (int)bi;
+    n[1] = (int)bj;
+  }
+  return (int)(bi * bj * bk);
 }
 
 Layout layout_for(long long N, const Tiling& t, int prec, int cap, bool stats, int axis_ni, long long ref_nodes) {
@@ -364,6 +390,7 @@ struct jz_solver {
   jz_params p;
   Phys ph;
   Tiling tl;
+  int nbricks, brick_n[2];  // bricks it advances in (along xi, eta), or 0: it marches in tiles (tl)
   Interior in;      // nodes the residual advances
   int cap;          // tiles the partial-sum arrays can hold
   Layout L;
@@ -403,8 +430,10 @@ struct jz_solver {
 
 namespace {
 
-// Shape, parameters, tiling and workspace layout of a solver (no device work).
-void setup_shape(jz_solver* s, int ni, int nj, int nk, const jz_params* p) {
+// Shape, parameters, tiling and workspace layout of a solver (no device
+// work).  bricks: whether it may advance in bricks, whose partial sums can
+// take a few more kilobytes than those of the tiles.
+void setup_shape(jz_solver* s, int ni, int nj, int nk, const jz_params* p, bool bricks) {
   s->ni = ni;
   s->nj = nj;
   s->nk = nk;
@@ -414,7 +443,8 @@ void setup_shape(jz_solver* s, int ni, int nj, int nk, const jz_params* p) {
   pick_tiling_for_device(ni, nj, nk, p, &s->tl);
   s->in = interior_of(ni, nj, nk, p);
   s->prec = p->precision;
-  s->cap = partial_capacity(ni, nj, nk, s->tl);
+  s->nbricks = bricks ? brick_count(ni, nj, nk, p, s->brick_n) : 0;
+  s->cap = partial_capacity(ni, nj, nk, s->tl, s->nbricks);
   s->L = layout_for(s->N, s->tl, s->prec, s->cap, p->stats_interval > 0, p->bc[2] == JZ_BC_AXIS ? ni : 0,
                     ref_nodes_of(ni, nj, nk, p));
   s->timing = false;
@@ -484,7 +514,8 @@ size_t jz_workspace_bytes(int ni, int nj, int nk, const jz_params* p) {
   if (!params_ok(p, &why) || !dims_ok(ni, nj, nk, p, &why)) return 0;
   Tiling t;
   pick_tiling(ni, nj, nk, p, &t);
-  return layout_for((long long)ni * nj * nk, t, p->precision, partial_capacity(ni, nj, nk, t), p->stats_interval > 0,
+  return layout_for((long long)ni * nj * nk, t, p->precision,
+                    partial_capacity(ni, nj, nk, t, brick_count(ni, nj, nk, p)), p->stats_interval > 0,
                     p->bc[2] == JZ_BC_AXIS ? ni : 0, ref_nodes_of(ni, nj, nk, p))
       .total;
 }
@@ -499,7 +530,9 @@ int jz_create(int ni, int nj, int nk, const jz_params* p, void* dev_workspace, s
   std::string why;
   if (!params_ok(p, &why) || !dims_ok(ni, nj, nk, p, &why)) return fail(JZ_EINVAL, "jz_create: %s", why.c_str());
   jz_solver* s = new jz_solver();
-  setup_shape(s, ni, nj, nk, p);
+  setup_shape(s, ni, nj, nk, p, true);
+  // a workspace without room for the bricks' partial sums: march
+  if (dev_workspace && ws_bytes < s->L.total) setup_shape(s, ni, nj, nk, p, false);
   s->stream = (hipStream_t)hip_stream;
   hipError_t e = hipGetDevice(&s->device);
   if (e != hipSuccess) {
@@ -792,7 +825,13 @@ static int advance_steps(jz_solver* s, int nsteps) {
         if (rc_ev) return rc_ev;
         HIP_TRY(hipEventRecord(e0, s->stream));
       }
-      HIP_TRY(launch_stage(s, a, k, ns, false));
+      if (s->nbricks > 0) {
+        a.tiles_i = s->brick_n[0];
+        a.tiles_j = s->brick_n[1];
+        HIP_TRY(launch_brick(a, s->prec == JZ_FP32_FLUX, s->flag, k, last, s->nbricks, s->stream));
+      } else {
+        HIP_TRY(launch_stage(s, a, k, ns, false));
+      }
       // the events bracket the stage kernel alone
       if (s->timing) {
         HIP_TRY(hipEventRecord(e1, s->stream));
@@ -808,7 +847,8 @@ static int advance_steps(jz_solver* s, int nsteps) {
         HIP_TRY(hipMemcpyAsync(s->q0, s->qa, 5 * s->N * sizeof(double), hipMemcpyDeviceToDevice, s->stream));
       in = out;
     }
-    HIP_TRY(launch_finalize_step(s->clock, s->norm_part, s->lam_part, s->tl.nblocks, step_ctl(s), s->flag,
+    const int parts = s->nbricks > 0 ? s->nbricks : s->tl.nblocks;
+    HIP_TRY(launch_finalize_step(s->clock, s->norm_part, s->lam_part, parts, step_ctl(s), s->flag,
                                  s->stream));
     if (s->stats && ++s->stat_steps % s->p.stats_interval == 0) {
       HIP_TRY(launch_stats_accumulate(s->q0, s->stats, s->N, s->p.gamma, s->stream));
@@ -1021,6 +1061,9 @@ int jz_set_tiling(jz_solver* s, int tile_i, int tile_j, int kchunk) {
   HIP_TRY(hipStreamSynchronize(s->stream));
   s->p = p;
   s->tl = t;
+  // back to the library's choice: bricks, if the partial sums have room for them
+  s->nbricks = brick_count(s->ni, s->nj, s->nk, &p, s->brick_n);
+  if (s->nbricks > s->cap) s->nbricks = 0;
   return JZ_OK;
 }
 
@@ -1107,7 +1150,8 @@ int jz_advance_static(int ni, int nj, int nk, const jz_params* p, const double* 
   if (p->stats_interval > 0)
     return fail(JZ_EINVAL, "jz_advance_static: time-averaged statistics need a solver (stats_interval must be 0)");
   jz_solver s{};
-  setup_shape(&s, ni, nj, nk, p);
+  setup_shape(&s, ni, nj, nk, p, true);
+  if (s.L.total > JZ_STATIC_SCRATCH_BYTES) setup_shape(&s, ni, nj, nk, p, false);
   if (s.L.total > JZ_STATIC_SCRATCH_BYTES)
     return fail(JZ_EINVAL, "jz_advance_static: a %dx%dx%d block needs %zu bytes of scratch, the static array holds %zu",
                 ni, nj, nk, s.L.total, (size_t)JZ_STATIC_SCRATCH_BYTES);

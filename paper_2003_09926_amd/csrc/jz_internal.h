@@ -68,6 +68,9 @@ struct Tiling {
   int nblocks;
 };
 
+// Bricks of owned nodes of the brick kernel (small blocks).
+constexpr int kBrickI = 8, kBrickJ = 8, kBrickK = 4;
+
 struct StageArgs {
   const void* qin;      // stencil input Q(k-1), node-major (double or float)
   const double* q0;     // Q(0), node-major doubles (read at the owned node only)
@@ -80,7 +83,7 @@ struct StageArgs {
   double alpha;         // stage coefficient
   long long N;
   int ni, nj, nk;
-  int tiles_i, tiles_j, kchunk, nchunks;
+  int tiles_i, tiles_j, kchunk, nchunks;  // (the brick kernel: bricks along xi and eta)
   Interior in;          // tiles and chunks cover [lo, hi) of each direction
   Phys ph;
   // FP32-flux intermediate stages of a block with physical faces: the double

@@ -46,13 +46,15 @@ __device__ inline float inv_cbrt(float J) {
   return r + r * (1.0f - J * r * r * r) * (1.0f / 3.0f);
 }
 
-// Contravariant fluxes F[d] of a node, the contravariant velocities Uc[d] and
+// Contravariant fluxes F[d] of a node (ONE: of direction only alone, if it is
+// not negative; the others are left unset), the contravariant velocities Uc[d] and
 // the sound speed, from its metrics m and J, its conserved variables Q and
 // the primitives (u, v, w, T, p) of the node (ctr) and of its six neighbours.
-template <typename Rl>
+template <bool ONE = false, typename Rl>
 __device__ __forceinline__ void node_fluxes(const Phys& ph, const Rl m[9], double Jg, const Rl Q[5], const Rl ctr[5],
                                             const Rl nxm[5], const Rl nxp[5], const Rl nym[5], const Rl nyp[5],
-                                            const Rl nzm[5], const Rl nzp[5], Rl F[3][5], Rl Uc[3], Rl& asnd) {
+                                            const Rl nzm[5], const Rl nzp[5], Rl F[3][5], Rl Uc[3], Rl& asnd,
+                                            int only = -1) {
   const Rl J = (Rl)Jg;
   // chain rule d phi / d x_a = J sum_d S^d_a delta_d phi, with the 1/2 of
   // the centred difference folded into the metric factor
@@ -105,6 +107,7 @@ __device__ __forceinline__ void node_fluxes(const Phys& ph, const Rl m[9], doubl
       const Rl sx = m[3 * d], sy = m[3 * d + 1], sz = m[3 * d + 2];
       const Rl U = fma(sz, uu[2], fma(sy, uu[1], sx * uu[0]));
       Uc[d] = U;
+      if (ONE && only >= 0 && only != d) continue;
       F[d][0] = Q[0] * U;
 #pragma unroll
       for (int r = 0; r < 3; ++r) {
