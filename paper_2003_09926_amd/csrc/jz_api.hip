@@ -44,22 +44,29 @@ hipError_t launch_check_met32(const float* m32, const double* jac, long long N, 
                               hipStream_t st);
 hipError_t launch_soa_to_met32(const double* src, float* m32, double* jac, long long N, hipStream_t st);
 hipError_t launch_soa_to_nodes(const double* src, double* dst, long long N, int C, hipStream_t st);
-hipError_t launch_nodes_to_soa(const double* src, double* dst, long long N, int C, hipStream_t st);
+hipError_t launch_nodes_to_soa(const double* src, double* dst, long long N, int C, const int* flag, Status* out,
+                               hipStream_t st);
 hipError_t launch_check_metrics(const double* m, long long N, int axis_ni, int axis_nj, int* flag, hipStream_t st);
-hipError_t launch_check_state(const double* q, long long N, double gm1, int* flag, hipStream_t st);
+hipError_t launch_check_state(const double* q, long long N, double gm1, int* verdict, hipStream_t st);
+hipError_t launch_take_state(const double* src, double* q0, long long N, const int* verdict, const void* met,
+                             const double* jac, bool met32, int ni, int nj, Interior in, double gamma, double* part,
+                             hipStream_t st);
+hipError_t launch_status(const Clock* clk, int* flag, int* verdict, bool reset, Status* out, hipStream_t st);
+hipError_t launch_begin(const double* m, const double* q, long long N, void* met, double* jac, double* q0, bool met32,
+                        int ni, int nj, Interior in, double gamma, double* part, Clock* clk, int* flag, hipStream_t st);
+hipError_t launch_end(const double* q0, double* q, long long N, const Clock* clk, const int* flag, double* out,
+                      hipStream_t st);
 int lambda_max_blocks(long long N);
 hipError_t launch_lambda_max(const double* q, const void* met, const double* jac, bool met32, long long N,
                              const int n[3], Interior in, double gamma, double* part, hipStream_t st);
 hipError_t launch_finalize_dt(Clock* clk, const double* lam_part, int nb, StepCtl ctl, int* flag, hipStream_t st);
 hipError_t launch_finalize_step(Clock* clk, const double* norm_part, const double* lam_part, int nb, StepCtl ctl,
                                 int* flag, hipStream_t st);
-hipError_t launch_reset_clock(Clock* clk, int* flag, hipStream_t st);
 hipError_t launch_domain_dt(const DomainSub* sub, int P, StepCtl ctl, hipStream_t st);
 hipError_t launch_domain_finalize(const DomainSub* sub, int P, StepCtl ctl, BatchCtl* work, double* part_red,
                                   hipStream_t st);
 hipError_t launch_halo_jobs(const HaloJob* jobs, int njobs, bool is_float, int d, long long max_count,
                             hipStream_t st);
-hipError_t launch_export_clock(const Clock* clk, const int* flag, double* out, hipStream_t st);
 }  // namespace jz
 
 using namespace jz;
@@ -410,7 +417,9 @@ struct jz_solver {
   double* norm_part;
   double* lam_part;
   Clock* clock;
-  int* flag;
+  int* flag;              // failure flag; flag[1]: verdict on new inputs, 0 between calls
+  Status* slot;           // pinned host memory the status kernel answers in (NULL: jz_advance_static)
+  bool lam_ready;         // lam_part holds the partials of the current state's first dt
   double* stats;          // sums of u, u^2, p, p^2 per node, or NULL
   double* axis_mean;      // centreline: azimuthal means per axial station, or NULL
   double* ref;            // FP32-flux far-field reference states, or NULL
@@ -471,7 +480,65 @@ void bind_workspace(jz_solver* s) {
   s->ref = s->L.ref ? (double*)(s->ws + s->L.ref) : nullptr;
   s->stat_samples = 0;
   s->stat_steps = 0;
-  s->grid_set = s->state_set = s->dt_valid = false;
+  s->grid_set = s->state_set = s->dt_valid = s->lam_ready = false;
+}
+
+// Pinned host memory in which solvers get their answers (clock, flag,
+// verdict): pages of 64 slots shared by the solvers of the process, since a
+// pinned allocation of its own would cost a solver more than its other set-up.
+// A page that empties is given back, except the last one (16 KiB).
+constexpr int kSlots = 64;
+constexpr size_t kSlotBytes = 256;
+static_assert(sizeof(Status) <= kSlotBytes, "a status exceeds its slot");
+struct SlotPage {
+  char* mem;
+  unsigned long long used;
+};
+std::mutex g_slot_mu;
+std::vector<SlotPage> g_slots;
+
+Status* slot_take() {
+  std::lock_guard<std::mutex> lock(g_slot_mu);
+  for (SlotPage& p : g_slots)
+    if (~p.used) {
+      const int k = __builtin_ctzll(~p.used);
+      p.used |= 1ull << k;
+      return (Status*)(p.mem + k * kSlotBytes);
+    }
+  void* mem = nullptr;
+  if (hipHostMalloc(&mem, kSlots * kSlotBytes, hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) !=
+      hipSuccess)
+    return nullptr;
+  g_slots.push_back(SlotPage{(char*)mem, 1ull});
+  return (Status*)mem;
+}
+
+void slot_give(Status* s) {
+  if (!s) return;
+  std::lock_guard<std::mutex> lock(g_slot_mu);
+  for (size_t i = 0; i < g_slots.size(); ++i) {
+    const long long off = (char*)s - g_slots[i].mem;
+    if (off < 0 || off >= (long long)(kSlots * kSlotBytes)) continue;
+    g_slots[i].used &= ~(1ull << (off / kSlotBytes));
+    if (g_slots[i].used == 0 && g_slots.size() > 1) {
+      (void)hipHostFree(g_slots[i].mem);
+      g_slots.erase(g_slots.begin() + i);
+    }
+    return;
+  }
+}
+
+// Whether kernels on device dev can read or write p directly: device memory
+// of that GPU, aligned as doubles.  Anything else (another GPU's memory,
+// managed or host memory passed as on_device) goes through a copy.
+bool direct_access(const void* p, int dev) {
+  if ((uintptr_t)p % sizeof(double)) return false;
+  hipPointerAttribute_t a;
+  if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return a.type == hipMemoryTypeDevice && a.device == dev;
 }
 
 }  // namespace
@@ -568,6 +635,7 @@ int jz_create(int ni, int nj, int nk, const jz_params* p, void* dev_workspace, s
   if (e == hipSuccess) e = hipMemcpyAsync(s->flag, z, sizeof z, hipMemcpyHostToDevice, s->stream);
   if (e == hipSuccess && s->stats) e = hipMemsetAsync(s->stats, 0, 4 * s->N * sizeof(double), s->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
+  if (e == hipSuccess && !(s->slot = slot_take())) e = hipErrorOutOfMemory;
   if (e != hipSuccess) {
     if (s->owns_ws) (void)hipFree(s->ws);
     delete s;
@@ -577,35 +645,29 @@ int jz_create(int ni, int nj, int nk, const jz_params* p, void* dev_workspace, s
   return JZ_OK;
 }
 
-static int read_flag(jz_solver* s, int* f) {
-  HIP_TRY(hipMemcpyAsync(f, s->flag, sizeof(int), hipMemcpyDeviceToHost, s->stream));
+// Clock, failure flag and verdict, read once everything queued is done (one
+// kernel and one wait; copies of a few bytes took 35 us each).  reset: new
+// inputs, the failure flag starts afresh.
+static int read_status(jz_solver* s, bool reset = false) {
+  HIP_TRY(launch_status(s->clock, s->flag, s->flag + 1, reset, s->slot, s->stream));
   HIP_TRY(hipStreamSynchronize(s->stream));
-  return JZ_OK;
-}
-
-static int clear_flag(jz_solver* s) {
-  const int z = 0;
-  HIP_TRY(hipMemcpyAsync(s->flag, &z, sizeof z, hipMemcpyHostToDevice, s->stream));
   return JZ_OK;
 }
 
 // Validate the installed metric set (J > 0 and every value finite).
 static int validate_metrics(jz_solver* s, const char* who) {
-  int rc = clear_flag(s);
-  if (rc) return rc;
   // the centreline of a cylindrical mesh (j = 0) carries no metrics
   const int axis_nj = s->p.bc[2] == JZ_BC_AXIS ? s->nj : 0;
   if (s->prec == JZ_FP64)
-    HIP_TRY(launch_check_metrics((const double*)s->met, s->N, s->ni, axis_nj, s->flag, s->stream));
+    HIP_TRY(launch_check_metrics((const double*)s->met, s->N, s->ni, axis_nj, s->flag + 1, s->stream));
   else
-    HIP_TRY(launch_check_met32((const float*)s->met, s->jac, s->N, s->ni, axis_nj, s->flag, s->stream));
-  int f = 0;
-  rc = read_flag(s, &f);
+    HIP_TRY(launch_check_met32((const float*)s->met, s->jac, s->N, s->ni, axis_nj, s->flag + 1, s->stream));
+  s->lam_ready = false;
+  int rc = read_status(s, true);
   if (rc) return rc;
+  const int f = s->slot->verdict;
   if (f) {
     s->grid_set = false;
-    clear_flag(s);
-    HIP_TRY(hipStreamSynchronize(s->stream));
     return fail(JZ_EINVAL, "%s: metric set has %s", who, (f & 1) ? "non-finite values" : "non-positive J");
   }
   s->grid_set = true;
@@ -629,13 +691,17 @@ int jz_set_grid_coords(jz_solver* s, const double* x, const double* y, const dou
 
 int jz_set_grid_metrics(jz_solver* s, const double* m, int on_device) {
   if (!s || !m) return fail(JZ_EINVAL, "jz_set_grid_metrics: NULL argument");
-  // stage the 10 x N array, then convert it to the stored layout
-  HIP_TRY(hipMemcpyAsync(s->qa, m, 10 * s->N * sizeof(double),
-                         on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, s->stream));
+  // convert the 10 x N array to the stored layout, where it lies or staged
+  const double* src = m;
+  if (!on_device || !direct_access(m, s->device)) {
+    HIP_TRY(hipMemcpyAsync(s->qa, m, 10 * s->N * sizeof(double),
+                           on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, s->stream));
+    src = s->qa;
+  }
   if (s->prec == JZ_FP64)
-    HIP_TRY(launch_soa_to_nodes(s->qa, (double*)s->met, s->N, 10, s->stream));
+    HIP_TRY(launch_soa_to_nodes(src, (double*)s->met, s->N, 10, s->stream));
   else
-    HIP_TRY(launch_soa_to_met32(s->qa, (float*)s->met, s->jac, s->N, s->stream));
+    HIP_TRY(launch_soa_to_met32(src, (float*)s->met, s->jac, s->N, s->stream));
   return validate_metrics(s, "jz_set_grid_metrics");
 }
 
@@ -643,7 +709,7 @@ int jz_get_grid_metrics(jz_solver* s, double* m, int on_device) {
   if (!s || !m) return fail(JZ_EINVAL, "jz_get_grid_metrics: NULL argument");
   if (!s->grid_set) return fail(JZ_ESTATE, "jz_get_grid_metrics: no grid set");
   if (s->prec == JZ_FP64) {
-    HIP_TRY(launch_nodes_to_soa((const double*)s->met, s->qa, s->N, 10, s->stream));
+    HIP_TRY(launch_nodes_to_soa((const double*)s->met, s->qa, s->N, 10, nullptr, nullptr, s->stream));
   } else {
     HIP_TRY(launch_met32_to_soa((const float*)s->met, s->jac, s->qa, s->N, s->stream));
   }
@@ -655,26 +721,27 @@ int jz_get_grid_metrics(jz_solver* s, double* m, int on_device) {
 
 int jz_set_state(jz_solver* s, const double* q, int on_device) {
   if (!s || !q) return fail(JZ_EINVAL, "jz_set_state: NULL argument");
-  // validate a node-major copy in Qa first so that a bad state leaves Q untouched
-  HIP_TRY(hipMemcpyAsync(s->qb, q, 5 * s->N * sizeof(double),
-                         on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, s->stream));
-  HIP_TRY(launch_soa_to_nodes(s->qb, s->qa, s->N, 5, s->stream));
-  int rc = clear_flag(s);
-  if (rc) return rc;
-  HIP_TRY(launch_check_state(s->qa, s->N, s->ph.gm1, s->flag, s->stream));
-  int f = 0;
-  rc = read_flag(s, &f);
-  if (rc) return rc;
-  if (f) {
-    clear_flag(s);
-    HIP_TRY(hipStreamSynchronize(s->stream));
-    if (f & 1) return fail(JZ_ENONFINITE, "jz_set_state: state holds NaN/Inf");
-    return fail(JZ_EINVAL, "jz_set_state: rho or p not positive somewhere");
+  // check the state where it lies (host memory: staged), then take it: a bad
+  // one leaves Q untouched.  120 bytes a node (200 with the spectral radii of
+  // its first dt, for which the metrics are read) in place of 280: a staging
+  // copy, a check and a copy after it are gone.
+  const double* src = q;
+  if (!on_device || !direct_access(q, s->device)) {
+    HIP_TRY(hipMemcpyAsync(s->qb, q, 5 * s->N * sizeof(double),
+                           on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, s->stream));
+    src = s->qb;
   }
-  HIP_TRY(hipMemcpyAsync(s->q0, s->qa, 5 * s->N * sizeof(double), hipMemcpyDeviceToDevice, s->stream));
-  HIP_TRY(hipStreamSynchronize(s->stream));
+  HIP_TRY(launch_check_state(src, s->N, s->ph.gm1, s->flag + 1, s->stream));
+  HIP_TRY(launch_take_state(src, s->q0, s->N, s->flag + 1, s->met, s->jac, s->prec == JZ_FP32_FLUX, s->ni, s->nj, s->in,
+                            s->p.gamma, s->grid_set ? s->lam_part : nullptr, s->stream));
+  int rc = read_status(s, true);
+  if (rc) return rc;
+  const int f = s->slot->verdict;
+  if (f & 1) return fail(JZ_ENONFINITE, "jz_set_state: state holds NaN/Inf");
+  if (f) return fail(JZ_EINVAL, "jz_set_state: rho or p not positive somewhere");
   s->state_set = true;
   s->dt_valid = false;
+  s->lam_ready = s->grid_set;
   return JZ_OK;
 }
 
@@ -716,10 +783,12 @@ static StepCtl step_ctl(jz_solver* s) {
 static int ensure_dt(jz_solver* s) {
   if (s->dt_valid) return JZ_OK;
   const int n[3] = {s->ni, s->nj, s->nk};
-  HIP_TRY(launch_lambda_max(s->q0, s->met, s->jac, s->prec == JZ_FP32_FLUX, s->N, n, s->in, s->p.gamma,
+  if (!s->lam_ready)
+    HIP_TRY(launch_lambda_max(s->q0, s->met, s->jac, s->prec == JZ_FP32_FLUX, s->N, n, s->in, s->p.gamma,
                             s->lam_part, s->stream));
   HIP_TRY(launch_finalize_dt(s->clock, s->lam_part, lambda_max_blocks(s->N), step_ctl(s), s->flag, s->stream));
   s->dt_valid = true;
+  s->lam_ready = false;
   return JZ_OK;
 }
 
@@ -865,33 +934,33 @@ int jz_advance(jz_solver* s, int nsteps) {
   return advance_steps(s, nsteps);
 }
 
-static int check_health(jz_solver* s) {
-  int f = 0;
-  int rc = read_flag(s, &f);
-  if (rc) return rc;
-  if (f) return fail(JZ_ENONFINITE, "a step produced NaN/Inf norms or a non-positive dt");
+static int health(const jz_solver* s) {
+  if (s->slot->flag) return fail(JZ_ENONFINITE, "a step produced NaN/Inf norms or a non-positive dt");
   return JZ_OK;
 }
 
 int jz_get_state(jz_solver* s, double* q, int on_device) {
   if (!s || !q) return fail(JZ_EINVAL, "jz_get_state: NULL argument");
   if (!s->state_set) return fail(JZ_ESTATE, "jz_get_state: no state set");
-  HIP_TRY(launch_nodes_to_soa(s->q0, s->qa, s->N, 5, s->stream));
-  HIP_TRY(hipMemcpyAsync(q, s->qa, 5 * s->N * sizeof(double),
-                         on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s->stream));
-  return check_health(s);
+  // straight into the caller's device buffer where a kernel can write it
+  const bool direct = on_device && direct_access(q, s->device);
+  HIP_TRY(launch_nodes_to_soa(s->q0, direct ? q : s->qa, s->N, 5, s->flag, s->slot, s->stream));
+  if (!direct)
+    HIP_TRY(hipMemcpyAsync(q, s->qa, 5 * s->N * sizeof(double),
+                           on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s->stream));
+  HIP_TRY(hipStreamSynchronize(s->stream));
+  return health(s);
 }
 
 int jz_get_residual_norms(jz_solver* s, double rms[5], double linf[5]) {
   if (!s || !rms || !linf) return fail(JZ_EINVAL, "jz_get_residual_norms: NULL argument");
-  Clock c;
-  HIP_TRY(hipMemcpyAsync(&c, s->clock, sizeof c, hipMemcpyDeviceToHost, s->stream));
-  int rc = check_health(s);
+  int rc = read_status(s);
+  if (rc) return rc;
   for (int v = 0; v < 5; ++v) {
-    rms[v] = c.rms[v];
-    linf[v] = c.linf[v];
+    rms[v] = s->slot->clock.rms[v];
+    linf[v] = s->slot->clock.linf[v];
   }
-  return rc;
+  return health(s);
 }
 
 int jz_get_clock(jz_solver* s, double* t, double* next_dt, long long* steps) {
@@ -900,13 +969,13 @@ int jz_get_clock(jz_solver* s, double* t, double* next_dt, long long* steps) {
     int rc = ensure_dt(s);
     if (rc) return rc;
   }
-  Clock c;
-  HIP_TRY(hipMemcpyAsync(&c, s->clock, sizeof c, hipMemcpyDeviceToHost, s->stream));
-  int rc = check_health(s);
+  int rc = read_status(s);
+  if (rc) return rc;
+  const Clock& c = s->slot->clock;
   if (t) *t = c.t;
   if (next_dt) *next_dt = c.dt;
   if (steps) *steps = c.steps;
-  return rc;
+  return health(s);
 }
 
 int jz_set_clock(jz_solver* s, double t, long long steps) {
@@ -927,10 +996,13 @@ int jz_eval_residual(jz_solver* s, double* r, int on_device) {
   StageArgs a = stage_args(s, s->q0, s->qa, 0.0);
   if (s->in.bnd) HIP_TRY(hipMemsetAsync(s->qa, 0, 5 * s->N * sizeof(double), s->stream));  // boundary layers: R = 0
   HIP_TRY(launch_stage(s, a, 0, s->p.n_stages, true));
-  HIP_TRY(launch_nodes_to_soa(s->qa, s->qb, s->N, 5, s->stream));
-  HIP_TRY(hipMemcpyAsync(r, s->qb, 5 * s->N * sizeof(double),
-                         on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s->stream));
-  return check_health(s);
+  const bool direct = on_device && direct_access(r, s->device);
+  HIP_TRY(launch_nodes_to_soa(s->qa, direct ? r : s->qb, s->N, 5, s->flag, s->slot, s->stream));
+  if (!direct)
+    HIP_TRY(hipMemcpyAsync(r, s->qb, 5 * s->N * sizeof(double),
+                           on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s->stream));
+  HIP_TRY(hipStreamSynchronize(s->stream));
+  return health(s);
 }
 
 int jz_eval_dt(jz_solver* s, double* dt, double* lambda_max) {
@@ -939,12 +1011,11 @@ int jz_eval_dt(jz_solver* s, double* dt, double* lambda_max) {
   s->dt_valid = false;
   int rc = ensure_dt(s);
   if (rc) return rc;
-  Clock c;
-  HIP_TRY(hipMemcpyAsync(&c, s->clock, sizeof c, hipMemcpyDeviceToHost, s->stream));
-  rc = check_health(s);
-  *dt = c.dt;
-  if (lambda_max) *lambda_max = c.lam_max;
-  return rc;
+  rc = read_status(s);
+  if (rc) return rc;
+  *dt = s->slot->clock.dt;
+  if (lambda_max) *lambda_max = s->slot->clock.lam_max;
+  return health(s);
 }
 
 int jz_stats_reset(jz_solver* s) {
@@ -1092,6 +1163,7 @@ int jz_destroy(jz_solver* s) {
   destroy_events(s->ev);
   destroy_events(s->ev_free);
   if (s->owns_ws) (void)hipFree(s->ws);
+  slot_give(s->slot);
   delete s;
   return JZ_OK;
 }
@@ -1164,18 +1236,14 @@ int jz_advance_static(int ni, int nj, int nk, const jz_params* p, const double* 
   s.stream = (hipStream_t)hip_stream;
   bind_workspace(&s);
   // a run that starts afresh: clock and flag cleared, state and metrics
-  // copied into the scratch layout
-  HIP_TRY(launch_reset_clock(s.clock, s.flag, s.stream));
-  if (s.prec == JZ_FP64)
-    HIP_TRY(launch_soa_to_nodes(met, (double*)s.met, s.N, 10, s.stream));
-  else
-    HIP_TRY(launch_soa_to_met32(met, (float*)s.met, s.jac, s.N, s.stream));
-  HIP_TRY(launch_soa_to_nodes(q, s.q0, s.N, 5, s.stream));
+  // copied into the scratch layout, the partials of the first dt
+  HIP_TRY(launch_begin(met, q, s.N, s.met, s.jac, s.q0, s.prec == JZ_FP32_FLUX, s.ni, s.nj, s.in, s.p.gamma, s.lam_part,
+                       s.clock, s.flag, s.stream));
+  s.lam_ready = true;
   s.grid_set = s.state_set = true;
   rc = advance_steps(&s, nsteps);
   if (rc) return rc;
-  HIP_TRY(launch_nodes_to_soa(s.q0, q, s.N, 5, s.stream));
-  if (info) HIP_TRY(launch_export_clock(s.clock, s.flag, info, s.stream));
+  HIP_TRY(launch_end(s.q0, q, s.N, s.clock, s.flag, info, s.stream));
   return JZ_OK;
 }
 

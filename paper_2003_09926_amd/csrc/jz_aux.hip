@@ -159,51 +159,6 @@ __global__ __launch_bounds__(256) void soa_to_met32_kernel(const double* __restr
   }
 }
 
-// flag |= 1 for a non-finite value, |= 2 for rho <= 0 or p <= 0
-__global__ __launch_bounds__(256) void check_state_kernel(const double* __restrict__ q, long long N, double gm1,
-                                                          int* __restrict__ flag) {
-  int bad = 0;
-  for (long long n = (long long)blockIdx.x * blockDim.x + threadIdx.x; n < N; n += (long long)gridDim.x * blockDim.x) {
-    double v[5];
-    for (int c = 0; c < 5; ++c) {
-      v[c] = q[5 * n + c];
-      if (!isfinite(v[c])) bad |= 1;
-    }
-    const double p = gm1 * (v[4] - 0.5 * (v[1] * v[1] + v[2] * v[2] + v[3] * v[3]) / v[0]);
-    if (!(v[0] > 0.0) || !(p > 0.0)) bad |= 2;
-  }
-  if (bad) atomicOr(flag, bad);
-}
-
-// per-block max of sum_d lambda^d (grid-stride; max is order-independent).
-// Uses the same metric view and arithmetic as the fused last stage, so the
-// dt of a restarted run is bitwise the dt of the uninterrupted one.
-template <bool MET32>
-__global__ __launch_bounds__(256) void lambda_max_kernel(const double* __restrict__ q, MetView<MET32> met,
-                                                         long long N, int ni, int nj, Interior in, double gamma,
-                                                         double* __restrict__ part) {
-  __shared__ double red[256];
-  double mx = 0.0;
-  for (long long n = (long long)blockIdx.x * blockDim.x + threadIdx.x; n < N; n += (long long)gridDim.x * blockDim.x) {
-    if (in.bnd) {  // boundary layers are not advanced and do not set dt
-      const int i = (int)(n % ni), j = (int)((n / ni) % nj), k = (int)(n / ((long long)ni * nj));
-      if (i < in.lo[0] || i >= in.hi[0] || j < in.lo[1] || j >= in.hi[1] || k < in.lo[2] || k >= in.hi[2]) continue;
-    }
-    double qq[5], mJ;
-    typename std::conditional<MET32, float, double>::type mm[9];
-    for (int c = 0; c < 5; ++c) qq[c] = q[5 * n + c];
-    met.load(n, mm, mJ);
-    mx = max_nan(mx, lambda_sum(qq, mm, mJ, gamma));
-  }
-  red[threadIdx.x] = mx;
-  __syncthreads();
-  for (int st = 128; st > 0; st >>= 1) {
-    if ((int)threadIdx.x < st) red[threadIdx.x] = max_nan(red[threadIdx.x], red[threadIdx.x + st]);
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) part[blockIdx.x] = red[0];
-}
-
 __global__ __launch_bounds__(256) void met32_to_soa_kernel(const float* __restrict__ m32, const double* __restrict__ jac,
                                                            double* __restrict__ dst, long long N) {
   for (long long n = (long long)blockIdx.x * blockDim.x + threadIdx.x; n < N; n += (long long)gridDim.x * blockDim.x) {
@@ -215,33 +170,70 @@ __global__ __launch_bounds__(256) void met32_to_soa_kernel(const float* __restri
 namespace {
 constexpr int FIN_T = 256;
 
-// Fixed-order reduction of nb partials: thread t folds b = t, t+256, ... in
-// order, then a fixed binary tree.  Bitwise reproducible for a given nb.
-__device__ double block_sum(const double* part, int stride, int nb, double* red) {
-  double acc = 0.0;
-  for (int b = threadIdx.x; b < nb; b += FIN_T) acc += part[(long long)b * stride];
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int st = FIN_T / 2; st > 0; st >>= 1) {
-    if ((int)threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
-    __syncthreads();
-  }
-  const double r = red[0];
-  __syncthreads();
-  return r;
+// Reductions of a step's nb partials by one workgroup of FIN_T threads, all
+// eleven quantities in one pass: thread t folds b = t, t + FIN_T, ... in
+// order, then a fixed tree over its wave, then the waves in order.  Bitwise
+// reproducible for a given nb.  (One quantity after another, each with a tree
+// of eight barriers over the workgroup, took 10.3 us for a handful of
+// partials and 33 us for 2,816; the bound is the latency of the loads.)
+__device__ inline double wave_sum(double v) {
+#pragma unroll
+  for (int st = 32; st > 0; st >>= 1) v += __shfl_down(v, st);
+  return v;
+}
+__device__ inline double wave_max(double v) {
+#pragma unroll
+  for (int st = 32; st > 0; st >>= 1) v = max_nan(v, __shfl_down(v, st));
+  return v;
 }
 
-__device__ double block_max(const double* part, int stride, int nb, double* red) {
-  double acc = 0.0;
-  for (int b = threadIdx.x; b < nb; b += FIN_T) acc = max_nan(acc, part[(long long)b * stride]);
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int st = FIN_T / 2; st > 0; st >>= 1) {
-    if ((int)threadIdx.x < st) red[threadIdx.x] = max_nan(red[threadIdx.x], red[threadIdx.x + st]);
-    __syncthreads();
+constexpr int FIN_W = FIN_T / 64;
+
+// out[0..4] sums and out[5..9] maxima of the norm partials, out[10] the
+// largest spectral radius; valid in thread 0
+__device__ void step_reduce(const double* __restrict__ norm_part, const double* __restrict__ lam_part, int nb,
+                            double (*red)[FIN_W], double out[11]) {
+  double acc[11];
+#pragma unroll
+  for (int q = 0; q < 11; ++q) acc[q] = 0.0;
+#pragma unroll 2
+  for (int b = threadIdx.x; b < nb; b += FIN_T) {
+    const double* __restrict__ p = norm_part + 10LL * b;
+#pragma unroll
+    for (int v = 0; v < 5; ++v) {
+      acc[v] += p[v];
+      acc[5 + v] = max_nan(acc[5 + v], p[5 + v]);
+    }
+    acc[10] = max_nan(acc[10], lam_part[b]);
   }
-  const double r = red[0];
+  const int w = threadIdx.x >> 6;
+#pragma unroll
+  for (int q = 0; q < 11; ++q) {
+    const double r = q < 5 ? wave_sum(acc[q]) : wave_max(acc[q]);
+    if ((threadIdx.x & 63) == 0) red[q][w] = r;
+  }
   __syncthreads();
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int q = 0; q < 11; ++q) {
+      double r = red[q][0];
+      for (int k = 1; k < FIN_W; ++k) r = q < 5 ? r + red[q][k] : max_nan(r, red[q][k]);
+      out[q] = r;
+    }
+  }
+}
+
+// maximum of nb values, valid in thread 0
+__device__ double block_max(const double* __restrict__ part, int nb, double* red) {
+  double acc = 0.0;
+#pragma unroll 4
+  for (int b = threadIdx.x; b < nb; b += FIN_T) acc = max_nan(acc, part[b]);
+  acc = wave_max(acc);
+  __syncthreads();  // red is free
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+  __syncthreads();
+  double r = red[0];
+  for (int k = 1; k < FIN_W; ++k) r = max_nan(r, red[k]);
   return r;
 }
 
@@ -251,8 +243,8 @@ __device__ double dt_rule(const StepCtl& c, double lmax) { return c.dt_fixed > 0
 // dt of the first step after a new state: from the lambda partials only
 __global__ __launch_bounds__(FIN_T) void finalize_dt_kernel(Clock* clk, const double* __restrict__ lam_part, int nb,
                                                             StepCtl ctl, int* __restrict__ flag) {
-  __shared__ double red[FIN_T];
-  const double lmax = block_max(lam_part, 1, nb, red);
+  __shared__ double red[FIN_W];
+  const double lmax = block_max(lam_part, nb, red);
   if (threadIdx.x == 0) {
     const double dt = dt_rule(ctl, lmax);
     clk->lam_max = lmax;
@@ -266,15 +258,14 @@ namespace {
 // norms, and set the next dt from the last stage's lambda partials
 __device__ void finalize_step_body(Clock* clk, const double* __restrict__ norm_part,
                                    const double* __restrict__ lam_part, int nb, const StepCtl& ctl,
-                                   int* __restrict__ flag, double* red) {
-  if (*flag) return;
-  double sums[5], maxs[5];
-  for (int v = 0; v < 5; ++v) {
-    sums[v] = block_sum(norm_part + v, 10, nb, red);
-    maxs[v] = block_max(norm_part + 5 + v, 10, nb, red);
-  }
-  const double lmax = block_max(lam_part, 1, nb, red);
-  if (threadIdx.x == 0) {
+                                   int* __restrict__ flag, double (*red)[FIN_W]) {
+  const int failed = *flag;  // looked at below, so that its load holds the others up no longer
+  double r[11];
+  step_reduce(norm_part, lam_part, nb, red, r);
+  if (threadIdx.x == 0 && !failed) {
+    const double* sums = r;
+    const double* maxs = r + 5;
+    const double lmax = r[10];
     bool ok = true;
     for (int v = 0; v < 5; ++v) {
       clk->rms[v] = sqrt(sums[v] * ctl.inv_n);
@@ -295,7 +286,7 @@ __device__ void finalize_step_body(Clock* clk, const double* __restrict__ norm_p
 __global__ __launch_bounds__(FIN_T) void finalize_step_kernel(Clock* clk, const double* __restrict__ norm_part,
                                                               const double* __restrict__ lam_part, int nb,
                                                               StepCtl ctl, int* __restrict__ flag) {
-  __shared__ double red[FIN_T];
+  __shared__ double red[11][FIN_W];
   finalize_step_body(clk, norm_part, lam_part, nb, ctl, flag, red);
 }
 
@@ -304,25 +295,205 @@ __global__ __launch_bounds__(FIN_T) void finalize_step_kernel(Clock* clk, const 
 // the stage launches for the next step
 __global__ __launch_bounds__(FIN_T) void finalize_batch_kernel(const BlockDesc* __restrict__ desc,
                                                                BatchCtl* __restrict__ ctl) {
-  __shared__ double red[FIN_T];
+  __shared__ double red[11][FIN_W];
   if (blockIdx.x == 0 && threadIdx.x < 5 * kBatchSlots) (&ctl->next[0][0])[threadIdx.x] = 0;
   if ((int)blockIdx.x >= ctl->nblk) return;
   const BlockDesc& D = desc[blockIdx.x];
   finalize_step_body(D.clock, D.norm_part, D.lam_part, D.ntiles, D.ctl, D.flag, red);
 }
 
-// structure-of-arrays (c x N, the ABI layout) <-> node-major (N x c, the
-// library's internal layout)
-__global__ __launch_bounds__(256) void soa_to_nodes_kernel(const double* __restrict__ src, double* __restrict__ dst,
-                                                           long long N, int C) {
-  for (long long n = (long long)blockIdx.x * blockDim.x + threadIdx.x; n < N; n += (long long)gridDim.x * blockDim.x)
-    for (int c = 0; c < C; ++c) dst[C * n + c] = src[c * N + n];
+// structure-of-arrays (C x N, the ABI layout) <-> node-major (N x C, the
+// library's internal layout), 256 nodes at a time through LDS, so that both
+// sides are read and written in whole lines.  Bound by HBM: nodes to arrays,
+// C = 5, 33.5 M nodes, 0.66 ms a node per thread, 0.50 ms (5.4 TB/s) this way.
+constexpr int TR_T = 256;
+template <int C>
+__global__ __launch_bounds__(TR_T) void soa_to_nodes_kernel(const double* __restrict__ src, double* __restrict__ dst,
+                                                            long long N) {
+  __shared__ double buf[TR_T * C];
+  const int t = threadIdx.x;
+  for (long long n0 = (long long)blockIdx.x * TR_T; n0 < N; n0 += (long long)gridDim.x * TR_T) {
+    const int cnt = (int)min((long long)TR_T, N - n0);
+    if (t < cnt) {
+#pragma unroll
+      for (int c = 0; c < C; ++c) buf[C * t + c] = src[c * N + n0 + t];
+    }
+    __syncthreads();
+    for (int e = t; e < cnt * C; e += TR_T) dst[C * n0 + e] = buf[e];
+    __syncthreads();
+  }
 }
 
-__global__ __launch_bounds__(256) void nodes_to_soa_kernel(const double* __restrict__ src, double* __restrict__ dst,
-                                                           long long N, int C) {
-  for (long long n = (long long)blockIdx.x * blockDim.x + threadIdx.x; n < N; n += (long long)gridDim.x * blockDim.x)
-    for (int c = 0; c < C; ++c) dst[c * N + n] = src[C * n + c];
+// flag, out: the failure flag and where to leave a copy of it for the host
+// (NULL: nowhere)
+template <int C>
+__global__ __launch_bounds__(TR_T) void nodes_to_soa_kernel(const double* __restrict__ src, double* __restrict__ dst,
+                                                            long long N, const int* __restrict__ flag,
+                                                            Status* __restrict__ out) {
+  __shared__ double buf[TR_T * C];
+  const int t = threadIdx.x;
+  if (out && blockIdx.x == 0 && t == 0) out->flag = *flag;
+  for (long long n0 = (long long)blockIdx.x * TR_T; n0 < N; n0 += (long long)gridDim.x * TR_T) {
+    const int cnt = (int)min((long long)TR_T, N - n0);
+    for (int e = t; e < cnt * C; e += TR_T) buf[e] = src[C * n0 + e];
+    __syncthreads();
+    if (t < cnt) {
+#pragma unroll
+      for (int c = 0; c < C; ++c) dst[c * N + n0 + t] = buf[C * t + c];
+    }
+    __syncthreads();
+  }
+}
+
+// A new state, checked where it lies (structure of arrays): verdict |= 1 for
+// a non-finite value, |= 2 for rho <= 0 or p <= 0.
+__global__ __launch_bounds__(256) void check_state_kernel(const double* __restrict__ q, long long N, double gm1,
+                                                          int* __restrict__ verdict) {
+  int bad = 0;
+  for (long long n = (long long)blockIdx.x * blockDim.x + threadIdx.x; n < N; n += (long long)gridDim.x * blockDim.x) {
+    double v[5];
+#pragma unroll
+    for (int c = 0; c < 5; ++c) {
+      v[c] = q[c * N + n];
+      if (!isfinite(v[c])) bad |= 1;
+    }
+    const double p = gm1 * (v[4] - 0.5 * (v[1] * v[1] + v[2] * v[2] + v[3] * v[3]) / v[0]);
+    if (!(v[0] > 0.0) || !(p > 0.0)) bad |= 2;
+  }
+  if (bad) atomicOr(verdict, bad);
+}
+
+// The spectral-radius sum of a node from its metrics in the stored layout
+// (the arithmetic of the fused last stage, so the dt of a restarted run is
+// bitwise the dt of the uninterrupted one); 0 on boundary layers, which are
+// not advanced and do not set dt.
+template <bool MET32>
+__device__ inline double node_lambda(const double q[5], const MetView<MET32>& met, long long n, int ni, int nj,
+                                     const Interior& in, double gamma) {
+  if (in.bnd) {
+    const int i = (int)(n % ni), j = (int)((n / ni) % nj), k = (int)(n / ((long long)ni * nj));
+    if (i < in.lo[0] || i >= in.hi[0] || j < in.lo[1] || j >= in.hi[1] || k < in.lo[2] || k >= in.hi[2]) return 0.0;
+  }
+  double mJ;
+  typename std::conditional<MET32, float, double>::type mm[9];
+  met.load(n, mm, mJ);
+  return lambda_sum(q, mm, mJ, gamma);
+}
+
+// largest value of a workgroup of 256 threads, to *out
+__device__ inline void block_lambda(double mx, double* red, double* __restrict__ out) {
+  mx = wave_max(mx);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
+  __syncthreads();
+  if (threadIdx.x == 0) *out = max_nan(max_nan(red[0], red[1]), max_nan(red[2], red[3]));
+}
+
+// per-block max of sum_d lambda^d (grid-stride; max is order-independent)
+template <bool MET32>
+__global__ __launch_bounds__(256) void lambda_max_kernel(const double* __restrict__ q, MetView<MET32> met,
+                                                         long long N, int ni, int nj, Interior in, double gamma,
+                                                         double* __restrict__ part) {
+  __shared__ double red[4];
+  double mx = 0.0;
+  for (long long n = (long long)blockIdx.x * blockDim.x + threadIdx.x; n < N; n += (long long)gridDim.x * blockDim.x) {
+    double qq[5];
+    for (int c = 0; c < 5; ++c) qq[c] = q[5 * n + c];
+    mx = max_nan(mx, node_lambda<MET32>(qq, met, n, ni, nj, in, gamma));
+  }
+  block_lambda(mx, red, part + blockIdx.x);
+}
+
+// An accepted state becomes Q(0): node-major, and with it the spectral-radius
+// partials of the first dt (part not NULL: the grid is set), in one pass over
+// it.  A rejected one (verdict) leaves the previous state.
+template <bool MET32>
+__global__ __launch_bounds__(TR_T) void take_state_kernel(const double* __restrict__ src, double* __restrict__ dst,
+                                                          long long N, const int* __restrict__ verdict,
+                                                          MetView<MET32> met, int ni, int nj, Interior in,
+                                                          double gamma, double* __restrict__ part) {
+  __shared__ double buf[TR_T * 5];
+  __shared__ double red[TR_T / 64];
+  if (*verdict) return;
+  const int t = threadIdx.x;
+  double mx = 0.0;
+  for (long long n0 = (long long)blockIdx.x * TR_T; n0 < N; n0 += (long long)gridDim.x * TR_T) {
+    const int cnt = (int)min((long long)TR_T, N - n0);
+    if (t < cnt) {
+      double q[5];
+#pragma unroll
+      for (int c = 0; c < 5; ++c) buf[5 * t + c] = q[c] = src[c * N + n0 + t];
+      if (part) mx = max_nan(mx, node_lambda<MET32>(q, met, n0 + t, ni, nj, in, gamma));
+    }
+    __syncthreads();
+    for (int e = t; e < cnt * 5; e += TR_T) dst[5 * n0 + e] = buf[e];
+    __syncthreads();
+  }
+  if (part) block_lambda(mx, red, part + blockIdx.x);
+}
+
+// Ends a call that answers the host: clock, flag and verdict to the pinned
+// slot.  reset: the inputs were new, so the flag starts afresh; the verdict is
+// always left at 0 for the next check.
+__global__ void status_kernel(const Clock* __restrict__ clk, int* __restrict__ flag, int* __restrict__ verdict, int reset,
+                              Status* __restrict__ out) {
+  if (threadIdx.x != 0) return;
+  out->clock = *clk;
+  out->verdict = *verdict;
+  *verdict = 0;
+  if (reset) *flag = 0;
+  out->flag = reset ? 0 : *flag;
+}
+
+// First launch of a run in the caller's buffers: metrics and state into the
+// stored layouts, the spectral-radius partials of the first dt, the clock and
+// the flag cleared (one launch for what took five of about 4.5 us each).
+template <bool MET32>
+__global__ __launch_bounds__(256) void begin_kernel(const double* __restrict__ m, const double* __restrict__ q, long long N,
+                                                    void* __restrict__ met, double* __restrict__ jac,
+                                                    double* __restrict__ q0, int ni, int nj, Interior in, double gamma,
+                                                    double* __restrict__ part, Clock* __restrict__ clk,
+                                                    int* __restrict__ flag) {
+  __shared__ double red[4];
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    Clock c;
+    c.t = 0.0;
+    c.dt = 0.0;
+    c.lam_max = 0.0;
+    for (int v = 0; v < 5; ++v) c.rms[v] = c.linf[v] = 0.0;
+    c.steps = 0;
+    c.flag = 0;
+    c.pad = 0;
+    *clk = c;
+    *flag = 0;
+  }
+  double mx = 0.0;
+  for (long long n = (long long)blockIdx.x * blockDim.x + threadIdx.x; n < N; n += (long long)gridDim.x * blockDim.x) {
+    typename std::conditional<MET32, float, double>::type mm[9];
+    double v[5];
+#pragma unroll
+    for (int c = 0; c < 5; ++c) v[c] = q[c * N + n];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) mm[k] = m[k * N + n];
+    const double J = m[9 * N + n];
+#pragma unroll
+    for (int c = 0; c < 5; ++c) q0[5 * n + c] = v[c];
+    if constexpr (MET32) {
+#pragma unroll
+      for (int k = 0; k < 9; ++k) ((float*)met)[9 * n + k] = mm[k];
+      jac[n] = J;
+    } else {
+#pragma unroll
+      for (int k = 0; k < 9; ++k) ((double*)met)[10 * n + k] = mm[k];
+      ((double*)met)[10 * n + 9] = J;
+    }
+    bool inside = true;
+    if (in.bnd) {
+      const int i = (int)(n % ni), j = (int)((n / ni) % nj), k = (int)(n / ((long long)ni * nj));
+      inside = i >= in.lo[0] && i < in.hi[0] && j >= in.lo[1] && j < in.hi[1] && k >= in.lo[2] && k < in.hi[2];
+    }
+    if (inside) mx = max_nan(mx, lambda_sum(v, mm, J, gamma));
+  }
+  block_lambda(mx, red, part + blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -439,18 +610,59 @@ hipError_t launch_soa_to_met32(const double* src, float* m32, double* jac, long 
   return hipGetLastError();
 }
 
-hipError_t launch_check_state(const double* q, long long N, double gm1, int* flag, hipStream_t st) {
-  hipLaunchKernelGGL(check_state_kernel, dim3(grid_stride_blocks(N)), dim3(256), 0, st, q, N, gm1, flag);
+hipError_t launch_check_state(const double* q, long long N, double gm1, int* verdict, hipStream_t st) {
+  hipLaunchKernelGGL(check_state_kernel, dim3(grid_stride_blocks(N)), dim3(256), 0, st, q, N, gm1, verdict);
+  return hipGetLastError();
+}
+
+// part NULL: without the spectral-radius partials (lambda_max_blocks(N) of them)
+hipError_t launch_take_state(const double* src, double* q0, long long N, const int* verdict, const void* met,
+                             const double* jac, bool met32, int ni, int nj, Interior in, double gamma, double* part,
+                             hipStream_t st) {
+  const dim3 grid(grid_stride_blocks(N)), block(TR_T);
+  if (met32) {
+    MetView<true> mv;
+    mv.m = (const float*)met;
+    mv.jac = jac;
+    hipLaunchKernelGGL(take_state_kernel<true>, grid, block, 0, st, src, q0, N, verdict, mv, ni, nj, in, gamma, part);
+  } else {
+    MetView<false> mv;
+    mv.m = (const double*)met;
+    mv.jac = jac;
+    hipLaunchKernelGGL(take_state_kernel<false>, grid, block, 0, st, src, q0, N, verdict, mv, ni, nj, in, gamma, part);
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_status(const Clock* clk, int* flag, int* verdict, bool reset, Status* out, hipStream_t st) {
+  hipLaunchKernelGGL(status_kernel, dim3(1), dim3(64), 0, st, clk, flag, verdict, reset ? 1 : 0, out);
   return hipGetLastError();
 }
 
 hipError_t launch_soa_to_nodes(const double* src, double* dst, long long N, int C, hipStream_t st) {
-  hipLaunchKernelGGL(soa_to_nodes_kernel, dim3(grid_stride_blocks(N)), dim3(256), 0, st, src, dst, N, C);
+  const dim3 grid(grid_stride_blocks(N)), block(TR_T);
+  if (C == 5) hipLaunchKernelGGL(soa_to_nodes_kernel<5>, grid, block, 0, st, src, dst, N);
+  else if (C == 10) hipLaunchKernelGGL(soa_to_nodes_kernel<10>, grid, block, 0, st, src, dst, N);
+  else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
-hipError_t launch_nodes_to_soa(const double* src, double* dst, long long N, int C, hipStream_t st) {
-  hipLaunchKernelGGL(nodes_to_soa_kernel, dim3(grid_stride_blocks(N)), dim3(256), 0, st, src, dst, N, C);
+hipError_t launch_nodes_to_soa(const double* src, double* dst, long long N, int C, const int* flag, Status* out,
+                               hipStream_t st) {
+  const dim3 grid(grid_stride_blocks(N)), block(TR_T);
+  if (C == 5) hipLaunchKernelGGL(nodes_to_soa_kernel<5>, grid, block, 0, st, src, dst, N, flag, out);
+  else if (C == 10) hipLaunchKernelGGL(nodes_to_soa_kernel<10>, grid, block, 0, st, src, dst, N, flag, out);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
+hipError_t launch_begin(const double* m, const double* q, long long N, void* met, double* jac, double* q0, bool met32,
+                        int ni, int nj, Interior in, double gamma, double* part, Clock* clk, int* flag, hipStream_t st) {
+  const dim3 grid(grid_stride_blocks(N)), block(256);
+  if (met32)
+    hipLaunchKernelGGL(begin_kernel<true>, grid, block, 0, st, m, q, N, met, jac, q0, ni, nj, in, gamma, part, clk, flag);
+  else
+    hipLaunchKernelGGL(begin_kernel<false>, grid, block, 0, st, m, q, N, met, jac, q0, ni, nj, in, gamma, part, clk, flag);
   return hipGetLastError();
 }
 
@@ -496,29 +708,13 @@ hipError_t launch_finalize_step(Clock* clk, const double* norm_part, const doubl
 }
 
 
-// Clock and failure flag of a run that starts afresh: time 0, step 0, no
-// failure (a kernel rather than a memset or a host copy, so that the work can
-// be captured in a graph).
-__global__ void reset_clock_kernel(Clock* __restrict__ clk, int* __restrict__ flag) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    Clock c;
-    c.t = 0.0;
-    c.dt = 0.0;
-    c.lam_max = 0.0;
-    for (int v = 0; v < 5; ++v) c.rms[v] = c.linf[v] = 0.0;
-    c.steps = 0;
-    c.flag = 0;
-    c.pad = 0;
-    *clk = c;
-    *flag = 0;
-  }
-}
-
-// Clock and flag as 14 doubles: t, dt of the next step, rms[5], linf[5],
-// steps, flag.
-__global__ void export_clock_kernel(const Clock* __restrict__ clk, const int* __restrict__ flag,
-                                    double* __restrict__ out) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
+// Last launch of a run in the caller's buffers: the state as a structure of
+// arrays, and (out not NULL) clock and flag as 14 doubles: t, dt of the next
+// step, rms[5], linf[5], steps, flag.
+__global__ __launch_bounds__(TR_T) void end_kernel(const double* __restrict__ q0, double* __restrict__ q, long long N,
+                                                   const Clock* __restrict__ clk, const int* __restrict__ flag,
+                                                   double* __restrict__ out) {
+  if (out && blockIdx.x == 0 && threadIdx.x == 0) {
     out[0] = clk->t;
     out[1] = clk->dt;
     for (int v = 0; v < 5; ++v) {
@@ -528,15 +724,15 @@ __global__ void export_clock_kernel(const Clock* __restrict__ clk, const int* __
     out[12] = (double)clk->steps;
     out[13] = (double)*flag;
   }
+  for (long long n = (long long)blockIdx.x * blockDim.x + threadIdx.x; n < N; n += (long long)gridDim.x * blockDim.x) {
+#pragma unroll
+    for (int c = 0; c < 5; ++c) q[c * N + n] = q0[5 * n + c];
+  }
 }
 
-hipError_t launch_reset_clock(Clock* clk, int* flag, hipStream_t st) {
-  hipLaunchKernelGGL(reset_clock_kernel, dim3(1), dim3(64), 0, st, clk, flag);
-  return hipGetLastError();
-}
-
-hipError_t launch_export_clock(const Clock* clk, const int* flag, double* out, hipStream_t st) {
-  hipLaunchKernelGGL(export_clock_kernel, dim3(1), dim3(64), 0, st, clk, flag, out);
+hipError_t launch_end(const double* q0, double* q, long long N, const Clock* clk, const int* flag, double* out,
+                      hipStream_t st) {
+  hipLaunchKernelGGL(end_kernel, dim3(grid_stride_blocks(N)), dim3(TR_T), 0, st, q0, q, N, clk, flag, out);
   return hipGetLastError();
 }
 
@@ -599,9 +795,9 @@ hipError_t launch_halo_jobs(const HaloJob* jobs, int njobs, bool is_float, int d
 // lambda^d over every sub-block's advanced nodes (the lambda_max partials),
 // written to every sub-block's clock.
 __global__ __launch_bounds__(FIN_T) void domain_dt_kernel(const DomainSub* __restrict__ sub, int P, StepCtl ctl) {
-  __shared__ double red[FIN_T];
+  __shared__ double red[FIN_W];
   double lmax = 0.0;
-  for (int p = 0; p < P; ++p) lmax = max_nan(lmax, block_max(sub[p].lam_part, 1, sub[p].nb_lmax, red));
+  for (int p = 0; p < P; ++p) lmax = max_nan(lmax, block_max(sub[p].lam_part, sub[p].nb_lmax, red));
   if (threadIdx.x == 0) {
     const double dt = dt_rule(ctl, lmax);
     const bool bad = !isfinite(lmax) || !isfinite(dt) || !(dt > 0.0);
@@ -618,19 +814,12 @@ __global__ __launch_bounds__(FIN_T) void domain_dt_kernel(const DomainSub* __res
 // in the sub-block's fixed tile order, to part_red[p][0..10].
 __global__ __launch_bounds__(FIN_T) void domain_part_reduce_kernel(const DomainSub* __restrict__ sub,
                                                                    double* __restrict__ part_red) {
-  __shared__ double red[FIN_T];
+  __shared__ double red[11][FIN_W];
   const DomainSub& S = sub[blockIdx.x];
-  double* out = part_red + 11 * blockIdx.x;
-  for (int v = 0; v < 5; ++v) {
-    const double sv = block_sum(S.norm_part + v, 10, S.nb_tiles, red);
-    const double mv = block_max(S.norm_part + 5 + v, 10, S.nb_tiles, red);
-    if (threadIdx.x == 0) {
-      out[v] = sv;
-      out[5 + v] = mv;
-    }
-  }
-  const double lm = block_max(S.lam_part, 1, S.nb_tiles, red);
-  if (threadIdx.x == 0) out[10] = lm;
+  double r[11];
+  step_reduce(S.norm_part, S.lam_part, S.nb_tiles, red, r);
+  if (threadIdx.x == 0)
+    for (int q = 0; q < 11; ++q) part_red[11 * blockIdx.x + q] = r[q];
 }
 
 // End of a domain step: the first-stage norms over all sub-blocks (their

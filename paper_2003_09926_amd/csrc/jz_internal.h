@@ -41,6 +41,14 @@ struct Clock {
   int pad;
 };
 
+// What a call that answers the host leaves in the solver's pinned slot: the
+// clock, the failure flag and the verdict on the last inputs checked.
+struct Status {
+  Clock clock;
+  int flag;
+  int verdict;
+};
+
 // Per-step reduction settings read by the finalize kernels.
 struct StepCtl {
   double cfl;
