@@ -36,8 +36,8 @@ hipError_t launch_stats_finalize(const double* acc, long long N, double inv_n, d
 hipError_t launch_stats_profile(const double* soa, long long N, int ni, int nj, int nk, int i, const int* bins,
                                 int nbins, double* out, hipStream_t st);
 hipError_t launch_bc(void* q, bool q_float, const double* q0, const void* met, const double* jac, bool met32,
-                     const int n[3], const int bc[6], double gamma, double mach_inf, double* axis_mean,
-                     const double* ref, hipStream_t st);
+                     const int n[3], const int bc[6], double gamma, double mach_inf, const double* ref,
+                     hipStream_t st);
 hipError_t launch_metrics_tl(const double* X, const double* period9, int ni, int nj, int nk, int bnd, void* m, double* jac,
                              bool met32, hipStream_t st);
 hipError_t launch_check_met32(const float* m32, const double* jac, long long N, int axis_ni, int axis_nj, int* flag,
@@ -104,7 +104,7 @@ size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 //              floats are the float stage states Q32a, Q32b) | metrics
 //              (9 floats per node) | J (1 double per node)
 struct Layout {
-  size_t q0, stage, q32a, q32b, met, jac, norm_part, lam_part, clock, flag, stats, axis, ref, total;
+  size_t q0, stage, q32a, q32b, met, jac, norm_part, lam_part, clock, flag, stats, ref, total;
   long long np;
 };
 
@@ -252,7 +252,7 @@ int brick_count(int ni, int nj, int nk, const jz_params* p, int n[2] = nullptr) 
   return (int)(bi * bj * bk);
 }
 
-Layout layout_for(long long N, const Tiling& t, int prec, int cap, bool stats, int axis_ni, long long ref_nodes) {
+Layout layout_for(long long N, const Tiling& t, int prec, int cap, bool stats, long long ref_nodes) {
   Layout L;
   std::memset(&L, 0, sizeof L);
   size_t off = 0;
@@ -279,9 +279,6 @@ Layout layout_for(long long N, const Tiling& t, int prec, int cap, bool stats, i
   L.flag = take(4 * sizeof(int));
   // time-averaged statistics: sums of u, u^2, p, p^2 per node (node-major)
   L.stats = stats ? take(4 * N * sizeof(double)) : 0;
-  // centreline: the azimuthal mean of the five conserved variables at each
-  // axial station (computed once per stage, read by every axis node)
-  L.axis = axis_ni > 0 ? take((size_t)axis_ni * 5 * sizeof(double)) : 0;
   // FP32-flux with physical faces: the double states of the far-field
   // reference planes (see StageArgs::ref)
   L.ref = ref_nodes > 0 ? take((size_t)ref_nodes * 5 * sizeof(double)) : 0;
@@ -421,7 +418,6 @@ struct jz_solver {
   Status* slot;           // pinned host memory the status kernel answers in (NULL: jz_advance_static)
   bool lam_ready;         // lam_part holds the partials of the current state's first dt
   double* stats;          // sums of u, u^2, p, p^2 per node, or NULL
-  double* axis_mean;      // centreline: azimuthal means per axial station, or NULL
   double* ref;            // FP32-flux far-field reference states, or NULL
   long long stat_samples; // samples in the sums
   long long stat_steps;   // steps since the last reset (samples every stats_interval)
@@ -454,7 +450,7 @@ void setup_shape(jz_solver* s, int ni, int nj, int nk, const jz_params* p, bool 
   s->prec = p->precision;
   s->nbricks = bricks ? brick_count(ni, nj, nk, p, s->brick_n) : 0;
   s->cap = partial_capacity(ni, nj, nk, s->tl, s->nbricks);
-  s->L = layout_for(s->N, s->tl, s->prec, s->cap, p->stats_interval > 0, p->bc[2] == JZ_BC_AXIS ? ni : 0,
+  s->L = layout_for(s->N, s->tl, s->prec, s->cap, p->stats_interval > 0,
                     ref_nodes_of(ni, nj, nk, p));
   s->timing = false;
   s->stage_ms_acc = 0;
@@ -476,7 +472,6 @@ void bind_workspace(jz_solver* s) {
   s->clock = (Clock*)(s->ws + s->L.clock);
   s->flag = (int*)(s->ws + s->L.flag);
   s->stats = s->L.stats ? (double*)(s->ws + s->L.stats) : nullptr;
-  s->axis_mean = s->L.axis ? (double*)(s->ws + s->L.axis) : nullptr;
   s->ref = s->L.ref ? (double*)(s->ws + s->L.ref) : nullptr;
   s->stat_samples = 0;
   s->stat_steps = 0;
@@ -583,7 +578,7 @@ size_t jz_workspace_bytes(int ni, int nj, int nk, const jz_params* p) {
   pick_tiling(ni, nj, nk, p, &t);
   return layout_for((long long)ni * nj * nk, t, p->precision,
                     partial_capacity(ni, nj, nk, t, brick_count(ni, nj, nk, p)), p->stats_interval > 0,
-                    p->bc[2] == JZ_BC_AXIS ? ni : 0, ref_nodes_of(ni, nj, nk, p))
+                    ref_nodes_of(ni, nj, nk, p))
       .total;
 }
 
@@ -910,7 +905,7 @@ static int advance_steps(jz_solver* s, int nsteps) {
       if (s->in.bnd) {
         const int n[3] = {s->ni, s->nj, s->nk};
         HIP_TRY(launch_bc(out, float_out, s->q0, s->met, s->jac, s->prec == JZ_FP32_FLUX, n, s->p.bc, s->p.gamma,
-                          s->p.mach_inf, s->axis_mean, float_out ? s->ref : nullptr, s->stream));
+                          s->p.mach_inf, float_out ? s->ref : nullptr, s->stream));
       }
       if (ns == 1)
         HIP_TRY(hipMemcpyAsync(s->q0, s->qa, 5 * s->N * sizeof(double), hipMemcpyDeviceToDevice, s->stream));
