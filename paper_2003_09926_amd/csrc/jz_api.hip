@@ -1255,10 +1255,9 @@ struct jz_batch {
   hipStream_t st;          // internal non-blocking stream (graph capture needs one)
   hipEvent_t ev_in, ev_out;
   BlockDesc* d_desc;       // member table (cap slots)
-  int* d_off;              // first global tile of each member (cap + 1)
+  int* d_off;              // first global tile of each member, first and later stages (2 (cap + 1))
   BatchCtl* d_ctl;         // work list read by the stage launches
   int cap;                 // member slots of the device tables
-  int total;               // tiles of all members
   long long npoints;
   bool fast;               // every member allows the FAST stage kernels (fast_form)
   bool use_graph, graph_ok;
@@ -1300,11 +1299,71 @@ void batch_drop_graph(jz_batch* b) {
 // change of the member set needs no new capture.
 // byte offsets of the parts of a staging buffer: work list, tile offsets, descriptors
 size_t stage_off_ofs() { return align_up(sizeof(BatchCtl)); }
-size_t stage_desc_ofs(int cap) { return align_up(stage_off_ofs() + (cap + 1) * sizeof(int)); }
+size_t stage_desc_ofs(int cap) { return align_up(stage_off_ofs() + 2 * (cap + 1) * sizeof(int)); }
 size_t stage_size(int cap) { return stage_desc_ofs(cap) + cap * sizeof(BlockDesc); }
 
-// The descriptor of a block as the persistent stage launches read it.
-void fill_desc(jz_solver* s, BlockDesc& D) {
+// Planes per chunk and tiles of member s in the stages after the first, for a
+// batch whose chunks hold up to kc planes (0: the member's own).
+int later_chunk(const jz_solver* s, int kc) {
+  if (kc <= 0 || s->p.kchunk > 0) return s->tl.kchunk;
+  const int ek = s->in.hi[2] - s->in.lo[2], n = (ek + kc - 1) / kc;
+  return (ek + n - 1) / n;
+}
+
+int later_tiles(const jz_solver* s, int kc) {
+  const int ek = s->in.hi[2] - s->in.lo[2], k = later_chunk(s, kc);
+  return s->tl.tiles_i * s->tl.tiles_j * ((ek + k - 1) / k);
+}
+
+// Chunk length of a batch's later stages where a member leaves it to the
+// library.  A member's own chunks are short enough to fill the device with
+// that member alone, and march two warm-up planes (and set-up worth about two
+// more) each; the members together need no such short ones.  With C planes a
+// chunk a stage takes about (all plane steps) / (workgroups resident) + C + 4:
+// the work, and the last tile of a slot.  Measured on 16 uneven blocks of 20 M
+// nodes, step with the members' chunks (8 to 20 planes) / 32 / 64 planes: FP64
+// 6.28 / 5.85 / 5.96 ms, FP32-flux 4.01 / 3.81 / 4.12.  (The first stage keeps
+// the members' chunks, since the RMS norms are summed chunk by chunk and are
+// those of the member alone.)
+int batch_chunk(const std::vector<jz_solver*>& m) {
+  if (m.empty()) return 0;
+  int dev = 0, ncu = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return 0;
+  if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+  const Tiling& t = m[0]->tl;
+  const long long slots =
+      (long long)ncu * (m[0]->prec == JZ_FP32_FLUX ? stage_wg_per_cu_fp32(t.bx, t.by) : stage_wg_per_cu_fp64(t.bx, t.by));
+  if (slots < 1) return 0;
+  int best = 0;
+  double least = 0;
+  for (int kc : {16, 20, 24, 32, 40, 48, 64}) {
+    double work = 0;
+    int longest = 0;
+    for (const jz_solver* s : m) {
+      const int ek = s->in.hi[2] - s->in.lo[2], k = later_chunk(s, kc), n = (ek + k - 1) / k;
+      work += (double)s->tl.tiles_i * s->tl.tiles_j * (ek + 4.0 * n);
+      longest = std::max(longest, k);
+    }
+    const double cost = work / slots + longest + 4;
+    if (best == 0 || cost < least) {
+      best = kc;
+      least = cost;
+    }
+  }
+  // the members' own chunks, if those are better (a batch too small to fill
+  // the device with longer ones)
+  double work = 0;
+  int longest = 0;
+  for (const jz_solver* s : m) {
+    work += (double)s->tl.tiles_i * s->tl.tiles_j * (s->in.hi[2] - s->in.lo[2] + 4.0 * s->tl.nchunks);
+    longest = std::max(longest, s->tl.kchunk);
+  }
+  return work / slots + longest + 4 <= least ? 0 : best;
+}
+
+// The descriptor of a block as the persistent stage launches read it (kc: see
+// later_chunk).
+void fill_desc(jz_solver* s, BlockDesc& D, int kc) {
   D.q0 = s->q0;
   D.bufA = s->prec == JZ_FP64 ? (void*)s->qa : (void*)s->q32a;
   D.bufB = s->prec == JZ_FP64 ? (void*)s->qb : (void*)s->q32b;
@@ -1323,38 +1382,49 @@ void fill_desc(jz_solver* s, BlockDesc& D) {
   D.kchunk = s->tl.kchunk;
   D.nchunks = s->tl.nchunks;
   D.ntiles = s->tl.nblocks;
+  D.kchunk_l = later_chunk(s, kc);
+  D.ntiles_l = later_tiles(s, kc);
   D.in = s->in;
   D.ctl = step_ctl(s);
   D.ph = s->ph;
 }
 
 // The work list of blocks m (tiles member by member, each in its logical
-// order) with zeroed counters.  The tile list is split among the slots by
-// plane steps: a tile of a chunk of L planes marches L + 2 of them, plus
-// about two planes' worth of set-up and reductions.
-void fill_worklist(const std::vector<jz_solver*>& m, BatchCtl& c) {
+// order) with zeroed counters, and the members' first tiles (off: two tables of
+// m.size() + 1).  The tile list is split among the slots by plane steps: a tile
+// of a chunk of L planes marches L + 2 of them, plus about two planes' worth of
+// set-up and reductions.
+void fill_worklist(const std::vector<jz_solver*>& m, int kc, BatchCtl& c, int* off) {
   std::memset(&c, 0, sizeof c);
   c.nblk = (int)m.size();
-  auto tile_cost = [](const jz_solver* s, int chunk) {
-    const int ek = s->in.hi[2] - s->in.lo[2];
-    const int len = std::min(s->tl.kchunk, ek - chunk * s->tl.kchunk);
-    return (long long)len + 4;
-  };
-  long long all = 0;
-  for (jz_solver* s : m)
-    for (int ch = 0; ch < s->tl.nchunks; ++ch) all += tile_cost(s, ch) * s->tl.tiles_i * s->tl.tiles_j;
-  int x = 1, g = 0;
-  long long acc = 0;
-  for (jz_solver* s : m)
-    for (int ch = 0; ch < s->tl.nchunks; ++ch) {
-      const long long w = tile_cost(s, ch);
-      for (int t = 0; t < s->tl.tiles_i * s->tl.tiles_j; ++t, ++g) {
-        while (x < kBatchSlots && acc * kBatchSlots >= all * x) c.split[x++] = g;
-        acc += w;
-      }
+  for (int later = 0; later < 2; ++later, off += m.size() + 1) {
+    auto chunk = [&](const jz_solver* s) { return later ? later_chunk(s, kc) : s->tl.kchunk; };
+    auto for_chunks = [&](const jz_solver* s, auto&& f) {
+      const int ek = s->in.hi[2] - s->in.lo[2], k = chunk(s);
+      for (int p = 0; p < ek; p += k) f((long long)std::min(k, ek - p) + 4);
+    };
+    long long all = 0;
+    off[0] = 0;
+    for (size_t i = 0; i < m.size(); ++i) {
+      const int tiles = m[i]->tl.tiles_i * m[i]->tl.tiles_j;
+      off[i + 1] = off[i];
+      for_chunks(m[i], [&](long long w) {
+        all += w * tiles;
+        off[i + 1] += tiles;
+      });
     }
-  while (x <= kBatchSlots) c.split[x++] = g;
-  c.total = g;
+    int x = 1, g = 0;
+    long long acc = 0;
+    int* split = c.split[later];
+    for (jz_solver* s : m)
+      for_chunks(s, [&](long long w) {
+        for (int t = 0; t < s->tl.tiles_i * s->tl.tiles_j; ++t, ++g) {
+          while (x < kBatchSlots && acc * kBatchSlots >= all * x) split[x++] = g;
+          acc += w;
+        }
+      });
+    while (x <= kBatchSlots) split[x++] = g;
+  }
 }
 
 int batch_tables(jz_batch* b) {
@@ -1367,15 +1437,13 @@ int batch_tables(jz_batch* b) {
   BlockDesc* d = reinterpret_cast<BlockDesc*>(h + stage_desc_ofs(b->cap));
   int* off = reinterpret_cast<int*>(h + stage_off_ofs());
   BatchCtl& c = *reinterpret_cast<BatchCtl*>(h);
-  off[0] = 0;
   b->npoints = 0;
+  const int kc = batch_chunk(b->m);
   for (int i = 0; i < n; ++i) {
-    fill_desc(b->m[i], d[i]);
-    off[i + 1] = off[i] + b->m[i]->tl.nblocks;
+    fill_desc(b->m[i], d[i], kc);
     b->npoints += b->m[i]->N;
   }
-  b->total = off[n];
-  fill_worklist(b->m, c);
+  fill_worklist(b->m, kc, c, off);
   // A member that does not allow the FAST kernels moves the batch to the
   // general ones, which serve every block, and a captured step with it (a new
   // capture follows; the last use of the old one has to end first).
@@ -1387,7 +1455,7 @@ int batch_tables(jz_batch* b) {
     b->fast = false;
   }
   if (n > 0) HIP_TRY(hipMemcpyAsync(b->d_desc, d, n * sizeof(BlockDesc), hipMemcpyHostToDevice, b->st));
-  HIP_TRY(hipMemcpyAsync(b->d_off, off, (n + 1) * sizeof(int), hipMemcpyHostToDevice, b->st));
+  HIP_TRY(hipMemcpyAsync(b->d_off, off, 2 * (n + 1) * sizeof(int), hipMemcpyHostToDevice, b->st));
   HIP_TRY(hipMemcpyAsync(b->d_ctl, &c, sizeof c, hipMemcpyHostToDevice, b->st));
   HIP_TRY(hipEventRecord(b->ev_stage[si], b->st));
   return JZ_OK;
@@ -1410,7 +1478,7 @@ int batch_reserve(jz_batch* b, int need) {
   BlockDesc* d = nullptr;
   int* o = nullptr;
   hipError_t e = hipMalloc((void**)&d, cap * sizeof(BlockDesc));
-  if (e == hipSuccess) e = hipMalloc((void**)&o, (cap + 1) * sizeof(int));
+  if (e == hipSuccess) e = hipMalloc((void**)&o, 2 * (cap + 1) * sizeof(int));
   if (e != hipSuccess) {
     if (d) (void)hipFree(d);
     return fail(JZ_ENOMEM, "batch tables: %s", hipGetErrorString(e));
@@ -2046,18 +2114,15 @@ int dom_build_launch_tables(jz_domain* D) {
   if (!D->batched) return JZ_OK;
   const int n = (int)D->sub.size();
   std::vector<BlockDesc> desc(n);
-  std::vector<int> off(n + 1, 0);
-  for (int i = 0; i < n; ++i) {
-    fill_desc(D->sub[i], desc[i]);
-    off[i + 1] = off[i] + D->sub[i]->tl.nblocks;
-  }
+  std::vector<int> off(2 * (n + 1), 0);
+  for (int i = 0; i < n; ++i) fill_desc(D->sub[i], desc[i], 0);
   BatchCtl c;
-  fill_worklist(D->sub, c);
+  fill_worklist(D->sub, 0, c, off.data());
   HIP_TRY(hipMalloc((void**)&D->d_desc, n * sizeof(BlockDesc)));
-  HIP_TRY(hipMalloc((void**)&D->d_off, (n + 1) * sizeof(int)));
+  HIP_TRY(hipMalloc((void**)&D->d_off, off.size() * sizeof(int)));
   HIP_TRY(hipMalloc((void**)&D->d_ctl, sizeof(BatchCtl)));
   HIP_TRY(hipMemcpy(D->d_desc, desc.data(), n * sizeof(BlockDesc), hipMemcpyHostToDevice));
-  HIP_TRY(hipMemcpy(D->d_off, off.data(), (n + 1) * sizeof(int), hipMemcpyHostToDevice));
+  HIP_TRY(hipMemcpy(D->d_off, off.data(), off.size() * sizeof(int), hipMemcpyHostToDevice));
   HIP_TRY(hipMemcpy(D->d_ctl, &c, sizeof c, hipMemcpyHostToDevice));
   return JZ_OK;
 }

@@ -189,9 +189,9 @@ __device__ inline double wave_max(double v) {
 
 constexpr int FIN_W = FIN_T / 64;
 
-// out[0..4] sums and out[5..9] maxima of the norm partials, out[10] the
-// largest spectral radius; valid in thread 0
-__device__ void step_reduce(const double* __restrict__ norm_part, const double* __restrict__ lam_part, int nb,
+// out[0..4] sums and out[5..9] maxima of the nb norm partials, out[10] the
+// largest of the nl spectral radii; valid in thread 0
+__device__ void step_reduce(const double* __restrict__ norm_part, const double* __restrict__ lam_part, int nb, int nl,
                             double (*red)[FIN_W], double out[11]) {
   double acc[11];
 #pragma unroll
@@ -204,8 +204,9 @@ __device__ void step_reduce(const double* __restrict__ norm_part, const double* 
       acc[v] += p[v];
       acc[5 + v] = max_nan(acc[5 + v], p[5 + v]);
     }
-    acc[10] = max_nan(acc[10], lam_part[b]);
   }
+#pragma unroll 4
+  for (int b = threadIdx.x; b < nl; b += FIN_T) acc[10] = max_nan(acc[10], lam_part[b]);
   const int w = threadIdx.x >> 6;
 #pragma unroll
   for (int q = 0; q < 11; ++q) {
@@ -257,11 +258,11 @@ namespace {
 // end of a step: advance the clock by the dt just used, store the first-stage
 // norms, and set the next dt from the last stage's lambda partials
 __device__ void finalize_step_body(Clock* clk, const double* __restrict__ norm_part,
-                                   const double* __restrict__ lam_part, int nb, const StepCtl& ctl,
+                                   const double* __restrict__ lam_part, int nb, int nl, const StepCtl& ctl,
                                    int* __restrict__ flag, double (*red)[FIN_W]) {
   const int failed = *flag;  // looked at below, so that its load holds the others up no longer
   double r[11];
-  step_reduce(norm_part, lam_part, nb, red, r);
+  step_reduce(norm_part, lam_part, nb, nl, red, r);
   if (threadIdx.x == 0 && !failed) {
     const double* sums = r;
     const double* maxs = r + 5;
@@ -287,7 +288,7 @@ __global__ __launch_bounds__(FIN_T) void finalize_step_kernel(Clock* clk, const 
                                                               const double* __restrict__ lam_part, int nb,
                                                               StepCtl ctl, int* __restrict__ flag) {
   __shared__ double red[11][FIN_W];
-  finalize_step_body(clk, norm_part, lam_part, nb, ctl, flag, red);
+  finalize_step_body(clk, norm_part, lam_part, nb, nb, ctl, flag, red);
 }
 
 // one workgroup per member slot of a batch (the table may hold fewer members
@@ -299,7 +300,7 @@ __global__ __launch_bounds__(FIN_T) void finalize_batch_kernel(const BlockDesc* 
   if (blockIdx.x == 0 && threadIdx.x < 5 * kBatchSlots) (&ctl->next[0][0])[threadIdx.x] = 0;
   if ((int)blockIdx.x >= ctl->nblk) return;
   const BlockDesc& D = desc[blockIdx.x];
-  finalize_step_body(D.clock, D.norm_part, D.lam_part, D.ntiles, D.ctl, D.flag, red);
+  finalize_step_body(D.clock, D.norm_part, D.lam_part, D.ntiles, D.ntiles_l, D.ctl, D.flag, red);
 }
 
 // structure-of-arrays (C x N, the ABI layout) <-> node-major (N x C, the
@@ -817,7 +818,7 @@ __global__ __launch_bounds__(FIN_T) void domain_part_reduce_kernel(const DomainS
   __shared__ double red[11][FIN_W];
   const DomainSub& S = sub[blockIdx.x];
   double r[11];
-  step_reduce(S.norm_part, S.lam_part, S.nb_tiles, red, r);
+  step_reduce(S.norm_part, S.lam_part, S.nb_tiles, S.nb_tiles, red, r);
   if (threadIdx.x == 0)
     for (int q = 0; q < 11; ++q) part_red[11 * blockIdx.x + q] = r[q];
 }

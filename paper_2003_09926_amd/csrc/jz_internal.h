@@ -118,7 +118,8 @@ struct BlockDesc {
   int* flag;
   long long N;
   int ni, nj, nk;
-  int tiles_i, tiles_j, kchunk, nchunks, ntiles;
+  int tiles_i, tiles_j, kchunk, nchunks, ntiles;  // first stage
+  int kchunk_l, ntiles_l;                         // later stages
   Interior in;
   StepCtl ctl;
   Phys ph;
@@ -135,8 +136,7 @@ struct BlockDesc {
 constexpr int kBatchSlots = 8;
 struct BatchCtl {
   int nblk;
-  int total;
-  int split[kBatchSlots + 1];
+  int split[2][kBatchSlots + 1];
   int next[5][kBatchSlots];
 };
 

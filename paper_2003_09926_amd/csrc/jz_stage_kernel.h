@@ -186,11 +186,11 @@ constexpr int stage_helper_vars() { return stage_helpers<Rl, BX, BY>() ? 3 : 0; 
 // a pitch of BX, the slots of one tile column lie BX elements apart and the
 // halo threads that walk a column hit the same LDS bank on every row; one
 // slot of padding per row spreads them over the banks.  The padding is taken
-// where the plane buffers of a stage with the primitive ring (39, plus the
-// partners' terms for two march steps; slots up to the last one a thread
-// uses: ring-2 corners have none; 32 bytes of alignment slack) still let the
-// CU hold the workgroups the register budget allows: two waves per SIMD in
-// FP64, three in the FP32-flux form.
+// where 39 plane buffers (the stages have 29, and the last one the metrics it
+// carries; plus the partners' terms for two march steps; slots up to the last
+// one a thread uses: ring-2 corners have none; 32 bytes of alignment slack)
+// still let the CU hold the workgroups the register budget allows: two waves
+// per SIMD in FP64, three in the FP32-flux form.
 template <typename Rl, int BX, int BY>
 constexpr long long lds_plane_bytes(int pitch) {
   return (39LL + 2 * stage_helper_vars<Rl, BX, BY>()) * ((BX - 2) + (long long)pitch * (BY - 1)) *
@@ -240,18 +240,14 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
 
   // The column's own primitives of planes s, s+1 and s+2 (the zeta
   // neighbours and the centre of the gradient plane) are kept in registers:
-  // one plane of primitives in LDS instead of a ring of three, and 15 fewer
-  // LDS reads per flux column.  Where the registers do not allow it, the
-  // stage keeps the ring: the FP32-flux first stage (norms at three waves
-  // per SIMD) and, in the batch kernel, whose tile loop holds more
-  // registers, every stage with reductions -- except in the compact FP64
-  // form, whose ring (93 KB of LDS) would leave one workgroup per CU: there
-  // the registers spill 40-48 bytes per lane instead, which costs less.
-  constexpr bool ZREG = BASE == 0 || ((!PERSIST || stage_compact<Rl, BX, BY>()) &&
-                                      (BASE == 2 || (BASE == 1 && sizeof(Rl) == 8)));
-  constexpr int NPR = ZREG ? 1 : 3;
+  // one plane of primitives in LDS, and 15 fewer LDS reads per flux column,
+  // against a ring of three planes.  (The stages with reductions of the
+  // FP32-flux form and of the batch kernel kept the ring while the general
+  // exponent's code took their registers; without it their batch stages
+  // measured 7 % faster in FP32-flux and 1 % in FP64, the FP32-flux single
+  // block the same.)
   // plane buffers (structure of arrays, one slot per tile column, rows of P)
-  __shared__ Rl sPr[NPR][5][NS];   // u, v, w, T, p: the gradient plane, or a ring of three planes
+  __shared__ Rl sPr[5][NS];   // u, v, w, T, p of the gradient plane
   // Q of the gradient plane, read in the owned phase after the second
   // barrier.  The compact form, whose LDS must hold two workgroups, keeps one
   // buffer and writes it after the first barrier of a march step (by then
@@ -280,7 +276,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
       (19LL + 5 * NQB + 2 * NHV) * NS * (long long)sizeof(Rl) + 2LL * NI * (9 * (long long)sizeof(MT) + 8) + 256;
   constexpr long long REG_WAVES = (sizeof(Rl) == 4 ? 3 : 2) * 4 * 64;
   constexpr long long REG_WG = REG_WAVES / NT > 0 ? REG_WAVES / NT : 1;
-  constexpr bool MET_LDS = BASE == 2 && ZREG && !PERSIST && MET_LDS_WG * REG_WG <= 160LL * 1024;
+  constexpr bool MET_LDS = BASE == 2 && MET_LDS_WG * REG_WG <= 160LL * 1024;
   __shared__ MT sMo[MET_LDS ? 2 : 1][MET_LDS ? 9 : 1][MET_LDS ? NI : 1];
   __shared__ double sMoJ[MET_LDS ? 2 : 1][MET_LDS ? NI : 1];
   // Compact form: Q of the next gradient plane of each edge thread's
@@ -426,9 +422,9 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
     out[3] = p.T;
     out[4] = p.p;
   };
-  auto write_prims = [&](int slot, const Rl pr[5]) {
+  auto write_prims = [&](const Rl pr[5]) {
 #pragma unroll
-    for (int k = 0; k < 5; ++k) sPr[slot][k][c] = pr[k];
+    for (int k = 0; k < 5; ++k) sPr[k][c] = pr[k];
   };
 
   // column registers: Q of planes s-1 (m), s, s+1 (g) and the lead s+2 (l)
@@ -446,10 +442,8 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
   Rl Qn[5], Mn[9];
   double MJn = 0.0;
 
-  // ring slots: plane k lives in slot (k - kbeg + 3) % 3
-  int slot_s = 1, slot_g = 2, slot_l = 0;  // planes kbeg-2, kbeg-1, kbeg
   // primitives of this column at planes s (PrM) and s+1 (PrC), carried in
-  // registers when ZREG
+  // registers
   Rl PrM[5] = {0, 0, 0, 0, 0}, PrC[5] = {0, 0, 0, 0, 0};
 #pragma unroll
   for (int v = 0; v < 5; ++v) Qs[v] = Qg[v] = Qn[v] = Qm[v] = 0;
@@ -462,10 +456,6 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
     if (COMPACT || isG) load_met(km, Mn, MJn);
     prims_of(Qs, PrM);
     prims_of(Qg, PrC);
-    if constexpr (!ZREG) {
-      write_prims(slot_s, PrM);
-      write_prims(slot_g, PrC);
-    }
   }
   // the second-ring column's first gradient plane
   if (hasB) qb_fetch(km);
@@ -501,7 +491,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
       lds_q(&sQB[0][0], 64, laneB, qb);
       prims_of(qb, pb);
 #pragma unroll
-      for (int k = 0; k < 5; ++k) sPr[ZREG ? 0 : slot_g][k][cB] = pb[k];
+      for (int k = 0; k < 5; ++k) sPr[k][cB] = pb[k];
     }
     // The compact form prefetches on every lane and, past the end of the
     // chunk, reloads the last plane it needs: the same loads on every path
@@ -509,8 +499,8 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
     // assuming they were skipped and waiting for everything in flight.
     if (s + 3 < kend + 2) kl = knext(kl);
     if (isP && (COMPACT || s + 3 < kend + 2)) load_q(kl, Qn);
-    // No barrier here: the primitive plane written now (slot_l; the single
-    // plane when ZREG) was last read in the previous step's gradient phase
+    // No barrier here: the primitive plane written now was last read in the
+    // previous step's gradient phase
     // (before its second barrier).  The Q, flux, scale and sensor buffers are
     // rewritten only after the next barrier, which every thread reaches after
     // finishing the owned phase.
@@ -530,8 +520,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
     Rl PrL[5];  // primitives of the lead plane
     if (isP) {
       prims_of(Ql, PrL);
-      if constexpr (ZREG) write_prims(0, PrC);  // the gradient plane s+1
-      else write_prims(slot_l, PrL);
+      write_prims(PrC);  // the gradient plane s+1
     }
     if constexpr (NQB == 2) write_q();
     __syncthreads();
@@ -586,7 +575,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
         }
         if (s + 2 < kend + 1) load_met(km, Mn, MJn);
       }
-      const Rl(*Pg)[NS] = sPr[ZREG ? 0 : slot_g];
+      const Rl(*Pg)[NS] = sPr;
       // Every primitive this column needs from the three planes, read in one
       // batch: the memory clobber keeps all the reads ahead of the arithmetic,
       // so their latencies overlap instead of adding up.
@@ -597,15 +586,9 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
         nxp[q] = Pg[q][c + 1];
         nym[q] = Pg[q][c - P];
         nyp[q] = Pg[q][c + P];
-        if constexpr (ZREG) {
-          ctr[q] = PrC[q];
-          nzm[q] = PrM[q];
-          nzp[q] = PrL[q];
-        } else {
-          ctr[q] = Pg[q][c];
-          nzm[q] = sPr[slot_s][q][c];
-          nzp[q] = sPr[slot_l][q][c];
-        }
+        ctr[q] = PrC[q];
+        nzm[q] = PrM[q];
+        nzp[q] = PrL[q];
       }
       asm volatile("" ::: "memory");
       Rl F[3][5], Uc[3], asnd;
@@ -789,7 +772,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
       for (int v = 0; v < 5; ++v) Acc[v] = (v < NV_OWN ? Rg[v] : Rl(0)) - Hp[v];
     }
 
-    // ---- shift the column registers and the ring by one plane ---------------
+    // ---- shift the column registers by one plane ---------------
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
       Qm[v] = Qs[v];
@@ -801,10 +784,6 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
     sigs = sigg;
     Js = Jg;
     ks = knext(ks);
-    const int old_s = slot_s;
-    slot_s = slot_g;
-    slot_g = slot_l;
-    slot_l = old_s;
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
       PrM[k] = PrC[k];
@@ -900,7 +879,9 @@ __attribute__((amdgpu_waves_per_eu(stage_waves_per_eu<Rl, BX, BY, MODE>()))) voi
   __shared__ int sTile;
   const int x = blockIdx.x % kBatchSlots;
   const int nblk = ctl->nblk;
-  const int lo = ctl->split[x], hi = ctl->split[x + 1];
+  const int later = stage > 0 ? 1 : 0;
+  const int lo = ctl->split[later][x], hi = ctl->split[later][x + 1];
+  tile_off += later * (nblk + 1);
   int* next = &ctl->next[stage][x];
   for (;;) {
     __syncthreads();  // the previous tile's LDS readers are done, and sTile is free
@@ -934,8 +915,7 @@ __attribute__((amdgpu_waves_per_eu(stage_waves_per_eu<Rl, BX, BY, MODE>()))) voi
     A.nk = D.nk;
     A.tiles_i = D.tiles_i;
     A.tiles_j = D.tiles_j;
-    A.kchunk = D.kchunk;
-    A.nchunks = D.nchunks;
+    A.kchunk = later ? D.kchunk_l : D.kchunk;
     A.in = D.in;
     A.ph = D.ph;
     stage_tile<Rl, TIn, TOut, MET32, BX, BY, MODE, FAST, true>(A, g - tile_off[a]);
