@@ -234,17 +234,24 @@ __device__ inline float sqrt_pos(float x) { return __builtin_amdgcn_sqrtf(x); }
 // radii in index units that set the CFL time step.  The nine scaled metrics
 // come in their stored type (double, or float in the FP32-flux form) and are
 // widened here, so every caller computes the same double result.
+// Every multiply-add is an explicit fma and nothing else is contracted, so
+// that each kernel it is inlined into rounds the same way.
 template <typename M>
 __device__ inline double lambda_sum(const double q[5], const M s[9], double J, double gamma) {
+#pragma clang fp contract(off)
   const double rinv = rcp_pos(q[0]);
   const double u = q[1] * rinv, v = q[2] * rinv, w = q[3] * rinv;
-  const double p = (gamma - 1.0) * (q[4] - 0.5 * q[0] * (u * u + v * v + w * w));
+  const double ke = fma(w, w, fma(u, u, v * v));
+  const double p = (gamma - 1.0) * fma(-(0.5 * q[0]), ke, q[4]);
   const double a = sqrt_pos(gamma * p * rinv);
+  const double aJ = a * J;
   double sum = 0.0;
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
     const double sx = (double)s[3 * d], sy = (double)s[3 * d + 1], sz = (double)s[3 * d + 2];
-    sum += fabs(J * (sx * u + sy * v + sz * w)) + a * J * sqrt_pos(sx * sx + sy * sy + sz * sz);
+    const double U = fma(sz, w, fma(sx, u, sy * v));
+    const double S = sqrt_pos(fma(sz, sz, fma(sx, sx, sy * sy)));
+    sum += fma(aJ, S, fabs(J * U));
   }
   return sum;
 }

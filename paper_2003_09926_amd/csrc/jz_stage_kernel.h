@@ -235,6 +235,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
   constexpr bool KEEP_REF = (MODE & 8) != 0 && std::is_same<TOut, float>::value && !PERSIST;
   constexpr int BASE = MODE & 7;  // the stage kind without bit 3
   constexpr bool COMPACT = stage_compact<Rl, BX, BY>();
+  constexpr bool UNIFORM = COMPACT || sizeof(Rl) == 4;  // prefetches on every lane
   static_assert(COMPACT ? NI + 2 * TI + 2 * TJ + 4 <= NT : TI * TJ + 4 * TI + 4 * TJ + 4 <= NT,
                 "tile roles exceed the workgroup");
 
@@ -357,7 +358,6 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
 
   const double dt = A.clock->dt;
   const double adt = A.alpha * dt;
-  const bool q0_is_input = (const void*)A.qin == (const void*)A.q0;
 
   // mapped plane index of k, and of the plane after mapped plane k.  (The
   // planes a chunk of a bounded direction reads all lie in the block: its
@@ -365,22 +365,28 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
   auto kmap = [&](int k) { return map_index(k, A.nk, bk); };
   auto knext = [&](int k) { return k + 1 == A.nk ? 0 : k + 1; };
   // C values of type T per node: the five of this column's node in mapped plane k
-  auto at = [&](auto* base, int C, int k) {
+  auto at_col = [&](auto* base, int C, int k, Off column) {
     typedef typename std::remove_pointer<decltype(base)>::type T;
     typedef typename std::conditional<std::is_const<T>::value, const char, char>::type Byte;
-    return (T*)((Byte*)(base + (long long)C * plane * k) + (Off)(col * (Off)(C * sizeof(T))));
+    return (T*)((Byte*)(base + (long long)C * plane * k) + (Off)(column * (Off)(C * sizeof(T))));
   };
-  auto load_q = [&](int k, Rl q[5]) {
+  auto at = [&](auto* base, int C, int k) { return at_col(base, C, k, col); };
+  auto load_q = [&](int k, TIn q[5]) {
     const TIn* w = at((const TIn*)A.qin, 5, k);
 #pragma unroll
-    for (int v = 0; v < 5; ++v) q[v] = (Rl)w[v];
+    for (int v = 0; v < 5; ++v) q[v] = w[v];
   };
+  // (lanes without fluxes: the metrics of the tile's first column, which its
+  // own lane loads anyway)
+  const Off colm = UNIFORM && !COMPACT && !isG
+                       ? (Off)map_index(i0, A.ni, bi) + (Off)A.ni * (Off)map_index(j0, A.nj, bj)
+                       : col;
   auto load_met = [&](int k, auto sm[9], double& J) {
     typedef typename std::conditional<MET32, float, double>::type MS;
-    const MS* w = at((const MS*)A.met, MET32 ? 9 : 10, k);
+    const MS* w = at_col((const MS*)A.met, MET32 ? 9 : 10, k, colm);
 #pragma unroll
     for (int v = 0; v < 9; ++v) sm[v] = w[v];
-    if constexpr (MET32) J = *at(A.jac, 1, k);
+    if constexpr (MET32) J = *at_col(A.jac, 1, k, colm);
     else J = w[9];
   };
   typedef __attribute__((address_space(3))) uint32_t* lds_u32;
@@ -439,7 +445,10 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
 
   // software prefetch, one march step ahead: Q of the next lead plane and
   // the metrics of the next gradient plane
-  Rl Qn[5], Mn[9];
+  // (Q as it is stored: converted on arrival, a double state read by the
+  // FP32-flux first stage would be waited for where the load is issued)
+  TIn Qn[5];
+  Rl Mn[9];
   double MJn = 0.0;
 
   // primitives of this column at planes s (PrM) and s+1 (PrC), carried in
@@ -447,13 +456,28 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
   Rl PrM[5] = {0, 0, 0, 0, 0}, PrC[5] = {0, 0, 0, 0, 0};
 #pragma unroll
   for (int v = 0; v < 5; ++v) Qs[v] = Qg[v] = Qn[v] = Qm[v] = 0;
+#pragma unroll
+  for (int k = 0; k < 9; ++k) Mn[k] = 0;
   // mapped planes: s (updated), s + 2 (metric prefetch), s + 3 (lead prefetch)
   int ks = kmap(kbeg - 2), km = kmap(kbeg - 1), kl = kmap(kbeg);
-  if (isP) {
-    load_q(ks, Qs);
-    load_q(km, Qg);
+  if (isP || UNIFORM) {
+    TIn q0[5], q1[5];
+    load_q(ks, q0);
+    load_q(km, q1);
     load_q(kl, Qn);
-    if (COMPACT || isG) load_met(km, Mn, MJn);
+    if (UNIFORM || isG) load_met(km, Mn, MJn);
+    // What the prologue loaded is waited for before the loop: a load still in
+    // flight at its entry would make every march step wait as the first does.
+#pragma unroll
+    for (int v = 0; v < 5; ++v) asm volatile("" : "+v"(Qn[v]));
+#pragma unroll
+    for (int k = 0; k < 9; ++k) asm volatile("" : "+v"(Mn[k]));
+    asm volatile("" : "+v"(MJn));
+#pragma unroll
+    for (int v = 0; v < 5; ++v) {
+      Qs[v] = (Rl)q0[v];
+      Qg[v] = (Rl)q1[v];
+    }
     prims_of(Qs, PrM);
     prims_of(Qg, PrC);
   }
@@ -482,7 +506,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
   auto march = [&](const int s) __attribute__((always_inline)) {
     // ---- lead plane s+2 (prefetched); prefetch plane s+3 -------------------
 #pragma unroll
-    for (int v = 0; v < 5; ++v) Ql[v] = Qn[v];
+    for (int v = 0; v < 5; ++v) Ql[v] = (Rl)Qn[v];
     // the second-ring column's gradient plane s+1, fetched during the
     // previous march step's gradient phase: nothing was issued after it
     if (hasB) {
@@ -493,12 +517,13 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
 #pragma unroll
       for (int k = 0; k < 5; ++k) sPr[k][cB] = pb[k];
     }
-    // The compact form prefetches on every lane and, past the end of the
-    // chunk, reloads the last plane it needs: the same loads on every path
-    // let the compiler count them when it waits for older loads, instead of
-    // assuming they were skipped and waiting for everything in flight.
+    // Prefetches are issued on every lane and, past the end of the chunk,
+    // reload the last plane it needs: the same loads on every path let the
+    // compiler count them when it waits for older loads, instead of assuming
+    // they were skipped and waiting for everything in flight, the previous
+    // plane's stores included.
     if (s + 3 < kend + 2) kl = knext(kl);
-    if (isP && (COMPACT || s + 3 < kend + 2)) load_q(kl, Qn);
+    if (UNIFORM || (isP && s + 3 < kend + 2)) load_q(kl, Qn);
     // No barrier here: the primitive plane written now was last read in the
     // previous step's gradient phase
     // (before its second barrier).  The Q, flux, scale and sensor buffers are
@@ -541,13 +566,15 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
     // stages of the compact form issue these loads as soon as the flux
     // contraction has freed its registers, the other stages and shapes (whose
     // registers do not allow that) just before the second barrier
-    constexpr bool Q0_IN_REGS = std::is_same<Rl, double>::value && std::is_same<TIn, double>::value;
+    // the first stage's stencil input is Q(0) itself, and in FP64 the column
+    // registers hold it exactly
+    constexpr bool Q0_IN_REGS = NORMS && std::is_same<Rl, double>::value && std::is_same<TIn, double>::value;
     double q0v[5];
     MT mo[9];
     double moJ;
     const bool upd = isI && s >= kbeg && !WRITE_R;  // plane s is updated in this step
     auto update_loads = [&]() {
-      if (!(Q0_IN_REGS && q0_is_input)) {
+      if constexpr (!Q0_IN_REGS) {
 #pragma unroll
         for (int v = 0; v < 5; ++v) q0v[v] = at(A.q0, 5, ks)[v];
       }
@@ -555,7 +582,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
     };
     if (s + 2 < kend + 1) km = knext(km);
     Rl m[9];
-    if constexpr (COMPACT) {
+    if constexpr (UNIFORM) {
 #pragma unroll
       for (int k = 0; k < 9; ++k) m[k] = move_apart(Mn[k]);
       Jg = move_apart(MJn);
@@ -564,16 +591,16 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
       if (hasB && s + 1 < kend) qb_fetch(km);
     }
     if (isG) {
-      if constexpr (!COMPACT) {
+      if constexpr (!UNIFORM) {
 #pragma unroll
         for (int k = 0; k < 9; ++k) m[k] = move_apart(Mn[k]);
         Jg = move_apart(MJn);
-        if (MET_LDS && t < NI) {
-#pragma unroll
-          for (int k = 0; k < 9; ++k) sMo[(s + 1) & 1][k][t] = (MT)m[k];
-          sMoJ[(s + 1) & 1][t] = Jg;
-        }
         if (s + 2 < kend + 1) load_met(km, Mn, MJn);
+      }
+      if (MET_LDS && t < NI) {
+#pragma unroll
+        for (int k = 0; k < 9; ++k) sMo[(s + 1) & 1][k][t] = (MT)m[k];
+        sMoJ[(s + 1) & 1][t] = Jg;
       }
       const Rl(*Pg)[NS] = sPr;
       // Every primitive this column needs from the three planes, read in one
@@ -691,6 +718,22 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
     // registers before the unrolled trips.  The FP32-flux form, whose rolled
     // trips give the Q(0) reads of the update more time, updates last.
     constexpr bool UPDATE_FIRST = sizeof(Rl) == 8;
+    // The update's loads are waited for by every lane, outside the branches:
+    // inside, the compiler takes them to be in flight still where the paths
+    // meet again, and waits there for everything, the plane's own stores to
+    // memory included (step at 512 x 256 x 256, with the uniform prefetches:
+    // FP64 8.61 -> 8.34 ms, FP32-flux 4.65 -> 4.43).
+    auto settle = [&]() {
+      if constexpr (!WRITE_R && !Q0_IN_REGS) {
+#pragma unroll
+        for (int v = 0; v < 5; ++v) asm volatile("" : "+v"(q0v[v]));
+      }
+      if constexpr (LAMMAX && !MET_LDS) {
+#pragma unroll
+        for (int k = 0; k < 9; ++k) asm volatile("" : "+v"(mo[k]));
+        asm volatile("" : "+v"(moJ));
+      }
+    };
     auto update = [&]() {
       if (HELP && s >= kbeg) {
         // the helper's terms of plane s (its variables) complete the carried sum
@@ -708,7 +751,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
           double qn[5];
           // In the first stage the stencil input is Q(0) itself and, in the
           // FP64 form, the column registers hold it exactly: no re-read.
-          if (Q0_IN_REGS && q0_is_input) {
+          if constexpr (Q0_IN_REGS) {
 #pragma unroll
             for (int v = 0; v < 5; ++v) qn[v] = (double)Qs[v] - adt * R[v];
           } else {
@@ -756,18 +799,24 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
         }
       }
     };
+    if constexpr (UPDATE_FIRST) settle();
+    Rl Rg[5];
     if (own) {
       if constexpr (UPDATE_FIRST) update();
-      Rl Rg[5];
       inplane(c, 0, NV_OWN, Rg);
       // the owner's variables sit in Rg[NHV..4]
       if (HELP) {
 #pragma unroll
         for (int v = 0; v < NV_OWN; ++v) Rg[v] = Rg[v + NHV];
       }
-      if constexpr (!UPDATE_FIRST) update();
-      // Acc: in-plane terms of plane g minus its lower zeta face; with HELP
-      // the helper's variables arrive next step, so only -Hp is carried
+    }
+    if constexpr (!UPDATE_FIRST) {
+      settle();
+      if (own) update();
+    }
+    // Acc: in-plane terms of plane g minus its lower zeta face; with HELP
+    // the helper's variables arrive next step, so only -Hp is carried
+    if (own) {
 #pragma unroll
       for (int v = 0; v < 5; ++v) Acc[v] = (v < NV_OWN ? Rg[v] : Rl(0)) - Hp[v];
     }

@@ -49,6 +49,25 @@ def test_periodic_bricks_equal_the_march(B, prec, dims):
 
 
 @pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("dims", [(45, 20, 37), (13, 9, 11)])
+def test_curvilinear_bricks_equal_the_march(B, prec, dims):
+    """Every metric component nonzero, strong noise: any multiply-add that one
+    kernel contracts and the other does not shows up."""
+    print(f"[gpu-case] bricks curvilinear precision={prec} {dims}", flush=True)
+    g = I.wavy_grid(*dims)
+    q = I.jet_state(g, 1.4, seed=9, noise=0.03)
+    got = []
+    for kw in ({}, TILE[prec], dict(tile_i=12, tile_j=12)):
+        with B.Solver(dims, B.params_default(precision=prec, re_d=2.0e3, **kw)) as s:
+            s.set_grid_coords(g.x, g.y, g.z, g.period)
+            s.set_state(q)
+            s.advance(4)
+            got.append((s.get_state(), s.clock(), s.residual_norms()))
+    _same(got[0], got[1])
+    _same(got[0], got[2])
+
+
+@pytest.mark.parametrize("prec", [0, 1])
 @pytest.mark.parametrize("kind", ["domain", "cylinder", "smallest"])
 def test_bounded_bricks_equal_the_march(B, prec, kind):
     print(f"[gpu-case] bricks bounded precision={prec} {kind}", flush=True)
