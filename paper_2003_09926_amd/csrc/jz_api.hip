@@ -161,6 +161,7 @@ void pick_tiling(int ni, int nj, int nk, const jz_params* p, Tiling* t, const In
   t->kchunk = kc;
   t->nchunks = (ek + kc - 1) / kc;
   t->nblocks = t->tiles_i * t->tiles_j * t->nchunks;
+  t->per_cu = t->ncu = 0;
 }
 
 // Planes per chunk when the caller leaves it to the library.  Every workgroup
@@ -199,6 +200,8 @@ void pick_tiling_for_device(int ni, int nj, int nk, const jz_params* p, Tiling* 
   const int per_cu = (p && p->precision == JZ_FP32_FLUX) ? stage_wg_per_cu_fp32(t->bx, t->by)
                                                           : stage_wg_per_cu_fp64(t->bx, t->by);
   if (per_cu < 1 || ncu < 1) return;
+  t->per_cu = per_cu;
+  t->ncu = ncu;
   const Interior in = over ? *over : interior_of(ni, nj, nk, p);
   const int ek = in.hi[2] - in.lo[2];
   // The compact FP64 shape (16 x 12 tiles, two workgroups per CU) runs its
@@ -220,23 +223,59 @@ void pick_tiling_for_device(int ni, int nj, int nk, const jz_params* p, Tiling* 
   t->nblocks = t->tiles_i * t->tiles_j * t->nchunks;
 }
 
+// Planes per chunk of a block that advances by itself with its launch shape
+// left to the library.  A tile marches its chunk and about four planes' worth
+// of warm-up and set-up; a round of one tile per workgroup slot takes that
+// long, and a last round that leaves half of every CU idle (two slots each)
+// about 0.7 of it.  So many short chunks pay where the tiles alone leave CUs
+// idle, and a number of chunks that fills the last round elsewhere.  Measured
+// steps with the chunks of pick_tiling_for_device / with these: FP64
+// 64 x 48 x 48 146 (8 planes) / 92 us (3), 96 x 64 x 96 207 (8) / 197 (7),
+// 192 x 192 x 192 2134 (64) / 1841 (24; 1790 with 48, which counts as 88 plane
+// times against 84), 320 x 160 x 160 2607 (64) / 2230 (32), 400 x 200 x 200
+// 4563 (64) / 4016 (34); FP32-flux 96 x 64 x 96 175 (8) / 137 (5),
+// 128 x 64 x 96 177 (8) / 155 (6).  (A block in a batch keeps the other
+// chunks, and so does one whose tile shape is given: its RMS norms are those
+// it has in a batch.)
+int own_kchunk(const Tiling& t, int ek, bool compact, int most) {
+  const long long tiles = (long long)t.tiles_i * t.tiles_j, slots = (long long)t.per_cu * t.ncu;
+  if (slots < 1) return t.kchunk;
+  int best = t.kchunk;
+  double least = 0;
+  for (int n = 1; n <= ek; ++n) {
+    const int kc = (ek + n - 1) / n;
+    const long long blocks = tiles * ((ek + kc - 1) / kc);
+    if (blocks > most) break;
+    if (compact && kc > 64) continue;  // (longer ones measured slower, 128 planes 6 % on 512 x 256 x 256)
+    const long long full = blocks / slots, rest = blocks % slots;
+    const double rounds = full + (rest == 0 ? 0.0 : t.per_cu > 1 && rest <= slots / t.per_cu ? 0.7 : 1.0);
+    const double cost = rounds * (kc + 4);
+    if (least == 0 || cost < least) {
+      best = kc;
+      least = cost;
+    }
+  }
+  return best;
+}
+
 // Tiles of the finest supported tiling (interior 12 x 4 tiles with 8-plane
 // chunks bounds every shape in either precision), so the partial-sum arrays
 // never need to grow when the tiling changes.
-int partial_capacity(int ni, int nj, int nk, const Tiling& t, int nbricks) {
-  const int fine = ((ni + 11) / 12) * ((nj + 3) / 4) * ((nk + 7) / 8);
-  return std::max(std::max(fine, t.nblocks), nbricks);
+int finest_tiles(int ni, int nj, int nk) { return ((ni + 11) / 12) * ((nj + 3) / 4) * ((nk + 7) / 8); }
+
+int partial_capacity(int ni, int nj, int nk, const Tiling& t, int own) {
+  return std::max(std::max(finest_tiles(ni, nj, nk), t.nblocks), own);
 }
 
 // Bricks a block is advanced in when the launch shape is left to the library
 // (0: it marches, see jz_brick.hip).  The bricks take about as many rounds as
 // there are bricks per workgroup slot, the march of a block this small the
-// time of its ten or so planes in turn, whatever its size.  Measured stage
-// launches, bricks / march: FP64 45 bricks (24 x 20 x 18) 10.4 / 32.9 us, 672
-// (61 x 47 x 53) 24.6 / 31.9, 1280 (80 x 64 x 64) 41.0 / 32.9, so three rounds
-// of one brick per CU; FP32-flux (two bricks per CU) 45 bricks 8.7 / 38.4 us,
-// 1280 22.5 / 36.5, 2160 (96 x 96 x 60) 36.2 / 37.0, so four rounds.
-constexpr int kMaxBricks64 = 768, kMaxBricks32 = 2048;
+// time of six or so planes in turn (own_kchunk).  Measured steps, bricks /
+// march: FP64 (one brick per CU, 256 a round) 45 bricks (24 x 20 x 18) 46 /
+// 86 us, 245 (48 x 40 x 28) 51 / 89, 288 (48 x 48 x 32) 84 / 79, 576 117 / 92;
+// FP32-flux (two per CU) 45 bricks 38 / 86 us, 1024 88 / 91, 1280 108 / 119,
+// 1408 123 / 119, 1536 127 / 120.
+constexpr int kMaxBricks64 = 256, kMaxBricks32 = 1280;
 
 int brick_count(int ni, int nj, int nk, const jz_params* p, int n[2] = nullptr) {
   if (p && (p->tile_i > 0 || p->kchunk > 0 || p->n_stages < 2 || p->tv_alpha != 0.5)) return 0;
@@ -250,6 +289,16 @@ int brick_count(int ni, int nj, int nk, const jz_params* p, int n[2] = nullptr) 
     n[1] = (int)bj;
   }
   return (int)(bi * bj * bk);
+}
+
+// Partial sums to have room for where the launch shape is left to the library:
+// the bricks, or two tiles on each CU of the device however small the block
+// (48 x 48 x 32 and the like have fewer of the finest tiles).
+constexpr int kOwnTiles = 512;
+
+int own_parts(int ni, int nj, int nk, const jz_params* p) {
+  if (p->tile_i > 0 || p->kchunk > 0) return 0;
+  return std::max(brick_count(ni, nj, nk, p), kOwnTiles);
 }
 
 Layout layout_for(long long N, const Tiling& t, int prec, int cap, bool stats, long long ref_nodes) {
@@ -394,7 +443,8 @@ struct jz_solver {
   jz_params p;
   Phys ph;
   Tiling tl;
-  int nbricks, brick_n[2];  // bricks it advances in (along xi, eta), or 0: it marches in tiles (tl)
+  int own_kc;               // planes per chunk of the tiles (tl) it marches in by itself
+  int nbricks, brick_n[2];  // bricks it advances in instead (along xi, eta), or 0
   Interior in;      // nodes the residual advances
   int cap;          // tiles the partial-sum arrays can hold
   Layout L;
@@ -435,10 +485,17 @@ struct jz_solver {
 
 namespace {
 
+void pick_own_chunk(jz_solver* s) {
+  const bool free = s->p.tile_i <= 0 && s->p.kchunk <= 0;
+  s->own_kc = !free ? s->tl.kchunk
+                    : own_kchunk(s->tl, s->in.hi[2] - s->in.lo[2], s->prec == JZ_FP64 && s->tl.bx == 20 && s->tl.by == 16,
+                                 std::min(s->cap, std::max(finest_tiles(s->ni, s->nj, s->nk), kOwnTiles)));
+}
+
 // Shape, parameters, tiling and workspace layout of a solver (no device
-// work).  bricks: whether it may advance in bricks, whose partial sums can
-// take a few more kilobytes than those of the tiles.
-void setup_shape(jz_solver* s, int ni, int nj, int nk, const jz_params* p, bool bricks) {
+// work).  room: whether the partial sums may take the few more kilobytes that
+// bricks and short chunks need (own_parts); without it the block marches.
+void setup_shape(jz_solver* s, int ni, int nj, int nk, const jz_params* p, bool room) {
   s->ni = ni;
   s->nj = nj;
   s->nk = nk;
@@ -448,8 +505,9 @@ void setup_shape(jz_solver* s, int ni, int nj, int nk, const jz_params* p, bool 
   pick_tiling_for_device(ni, nj, nk, p, &s->tl);
   s->in = interior_of(ni, nj, nk, p);
   s->prec = p->precision;
-  s->nbricks = bricks ? brick_count(ni, nj, nk, p, s->brick_n) : 0;
-  s->cap = partial_capacity(ni, nj, nk, s->tl, s->nbricks);
+  s->nbricks = room ? brick_count(ni, nj, nk, p, s->brick_n) : 0;
+  s->cap = partial_capacity(ni, nj, nk, s->tl, room ? own_parts(ni, nj, nk, p) : 0);
+  pick_own_chunk(s);
   s->L = layout_for(s->N, s->tl, s->prec, s->cap, p->stats_interval > 0,
                     ref_nodes_of(ni, nj, nk, p));
   s->timing = false;
@@ -577,7 +635,7 @@ size_t jz_workspace_bytes(int ni, int nj, int nk, const jz_params* p) {
   Tiling t;
   pick_tiling(ni, nj, nk, p, &t);
   return layout_for((long long)ni * nj * nk, t, p->precision,
-                    partial_capacity(ni, nj, nk, t, brick_count(ni, nj, nk, p)), p->stats_interval > 0,
+                    partial_capacity(ni, nj, nk, t, own_parts(ni, nj, nk, p)), p->stats_interval > 0,
                     ref_nodes_of(ni, nj, nk, p))
       .total;
 }
@@ -806,7 +864,7 @@ static double stage_bytes(jz_solver* s, int stage) {
 static hipError_t launch_stage(jz_solver* s, const StageArgs& a, int k, int ns, bool residual_only) {
   if (s->prec == JZ_FP64) {
     int mode = residual_only ? 4 : ((k == 0 ? 1 : 0) | (k == ns - 1 ? 2 : 0));
-    return launch_stage_fp64(a, s->flag, mode, s->tl.bx, s->tl.by, s->tl.nblocks, s->stream);
+    return launch_stage_fp64(a, s->flag, mode, s->tl.bx, s->tl.by, a.tiles_i * a.tiles_j * a.nchunks, s->stream);
   }
   int kind;
   if (residual_only)
@@ -819,7 +877,7 @@ static hipError_t launch_stage(jz_solver* s, const StageArgs& a, int k, int ns, 
     kind = 2;
   else
     kind = 1;
-  return launch_stage_fp32(a, s->flag, kind, s->tl.bx, s->tl.by, s->tl.nblocks, s->stream);
+  return launch_stage_fp32(a, s->flag, kind, s->tl.bx, s->tl.by, a.tiles_i * a.tiles_j * a.nchunks, s->stream);
 }
 
 // Event pairs for the stage timing come from a pool that jz_set_timing fills
@@ -866,6 +924,7 @@ static int advance_steps(jz_solver* s, int nsteps) {
   int rc = ensure_dt(s);
   if (rc) return rc;
   const int ns = s->p.n_stages;
+  const int own_chunks = (s->in.hi[2] - s->in.lo[2] + s->own_kc - 1) / s->own_kc;
   for (int step = 0; step < nsteps; ++step) {
     // buffer rotation: Q0 -> A -> B -> A -> B -> Q0 (last stage in place:
     // Q(0) is read only at the node being written).  A and B are double
@@ -894,6 +953,8 @@ static int advance_steps(jz_solver* s, int nsteps) {
         a.tiles_j = s->brick_n[1];
         HIP_TRY(launch_brick(a, s->prec == JZ_FP32_FLUX, s->flag, k, last, s->nbricks, s->stream));
       } else {
+        a.kchunk = s->own_kc;
+        a.nchunks = own_chunks;
         HIP_TRY(launch_stage(s, a, k, ns, false));
       }
       // the events bracket the stage kernel alone
@@ -911,7 +972,7 @@ static int advance_steps(jz_solver* s, int nsteps) {
         HIP_TRY(hipMemcpyAsync(s->q0, s->qa, 5 * s->N * sizeof(double), hipMemcpyDeviceToDevice, s->stream));
       in = out;
     }
-    const int parts = s->nbricks > 0 ? s->nbricks : s->tl.nblocks;
+    const int parts = s->nbricks > 0 ? s->nbricks : s->tl.tiles_i * s->tl.tiles_j * own_chunks;
     HIP_TRY(launch_finalize_step(s->clock, s->norm_part, s->lam_part, parts, step_ctl(s), s->flag,
                                  s->stream));
     if (s->stats && ++s->stat_steps % s->p.stats_interval == 0) {
@@ -1128,6 +1189,7 @@ int jz_set_tiling(jz_solver* s, int tile_i, int tile_j, int kchunk) {
   s->p = p;
   s->tl = t;
   // back to the library's choice: bricks, if the partial sums have room for them
+  pick_own_chunk(s);
   s->nbricks = brick_count(s->ni, s->nj, s->nk, &p, s->brick_n);
   if (s->nbricks > s->cap) s->nbricks = 0;
   return JZ_OK;
@@ -1901,14 +1963,21 @@ int jz_batch_autotune(jz_batch* b, int trial_steps, const char* cache_path, int*
   }
   // apply the choice to every member, or to none (a cached choice that a
   // member does not take leaves the batch as it was)
-  std::vector<std::pair<jz_params, Tiling>> old;
-  for (jz_solver* s : b->m) old.emplace_back(s->p, s->tl);
+  struct Shape {
+    jz_params p;
+    Tiling tl;
+    int own_kc, nbricks;
+  };
+  std::vector<Shape> old;
+  for (jz_solver* s : b->m) old.push_back({s->p, s->tl, s->own_kc, s->nbricks});
   for (size_t i = 0; i < b->m.size(); ++i) {
     int rc = jz_set_tiling(b->m[i], best_ti, best_tj, best_kc);
     if (rc) {
       for (size_t j = 0; j < i; ++j) {
-        b->m[j]->p = old[j].first;
-        b->m[j]->tl = old[j].second;
+        b->m[j]->p = old[j].p;
+        b->m[j]->tl = old[j].tl;
+        b->m[j]->own_kc = old[j].own_kc;
+        b->m[j]->nbricks = old[j].nbricks;
       }
       return rc;
     }

@@ -1,13 +1,11 @@
 // jz_brick.hip -- one Runge-Kutta stage of a small block, brick by brick.
 //
 // The marching stage kernel (jz_stage_kernel.h) walks the planes of a chunk
-// one after another, about 2.7 us a plane, and a block of a few hundred
-// thousand nodes has too few tiles to fill the device with chunks of useful
-// length: its stages take the time of ten or more planes in turn however
-// small the block is.  Here a workgroup takes a brick of 8 x 8 x 4 owned
-// nodes and computes every flux it needs at once, one node per thread: the
-// 256 owned nodes and the 256 nodes next to its faces (twice the flux work
-// per owned node, against 1.3 x (planes + 2) / planes for the march).
+// one after another, about 2.2 us a plane, with some four planes' worth of
+// warm-up and set-up: 14 us a stage even for chunks of one plane.  Here a
+// workgroup takes a brick of 8 x 8 x 4 owned nodes and computes every flux it
+// needs at once, one node per thread: the 256 owned nodes and the 256 nodes
+// next to its faces (twice the flux work per owned node).
 //   phase 1  every thread loads its node (Q, metrics) and, for 336 of them,
 //            a second one that only supplies primitives and Q (the second
 //            ring, and the first ring's edges); primitives and Q to LDS
@@ -15,8 +13,9 @@
 //            halo node keeps those of its face's direction only
 //   phase 3  residual and update: the owner of a node takes two of the five
 //            variables, the thread 256 above it three
-// Measured, the step of a 24 x 20 x 18 block: FP64 162 us marching, 51 us in
-// bricks, FP32-flux 189 and 43 us (64 x 48 x 48: 157 and 126, 180 and 82 us).
+// Measured, the step of a 24 x 20 x 18 block: FP64 86 us marching, 46 us in
+// bricks, FP32-flux 86 and 38 us (48 x 40 x 28 FP64: 89 and 51 us, 48 x 48 x 48
+// FP32-flux: 89 and 53 us).
 // What bounds it: for the smallest blocks the chain of the three phases in
 // one workgroup (two waves per SIMD, one workgroup per CU in FP64), for larger
 // ones the doubled flux work, which is why large blocks march.

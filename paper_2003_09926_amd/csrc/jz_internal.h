@@ -74,6 +74,7 @@ struct Tiling {
   int kchunk;         // planes marched per workgroup
   int tiles_i, tiles_j, nchunks;
   int nblocks;
+  int per_cu, ncu;    // workgroups resident per CU, CUs of the device (0: not known)
 };
 
 // Bricks of owned nodes of the brick kernel (small blocks).
