@@ -170,29 +170,18 @@ __global__ __launch_bounds__(256) void met32_to_soa_kernel(const float* __restri
 namespace {
 constexpr int FIN_T = 256;
 
-// Reductions of a step's nb partials by one workgroup of FIN_T threads, all
-// eleven quantities in one pass: thread t folds b = t, t + FIN_T, ... in
-// order, then a fixed tree over its wave, then the waves in order.  Bitwise
-// reproducible for a given nb.  (One quantity after another, each with a tree
-// of eight barriers over the workgroup, took 10.3 us for a handful of
-// partials and 33 us for 2,816; the bound is the latency of the loads.)
-__device__ inline double wave_sum(double v) {
-#pragma unroll
-  for (int st = 32; st > 0; st >>= 1) v += __shfl_down(v, st);
-  return v;
-}
-__device__ inline double wave_max(double v) {
-#pragma unroll
-  for (int st = 32; st > 0; st >>= 1) v = max_nan(v, __shfl_down(v, st));
-  return v;
-}
-
 constexpr int FIN_W = FIN_T / 64;
 
-// out[0..4] sums and out[5..9] maxima of the nb norm partials, out[10] the
-// largest of the nl spectral radii; valid in thread 0
-__device__ void step_reduce(const double* __restrict__ norm_part, const double* __restrict__ lam_part, int nb, int nl,
-                            double (*red)[FIN_W], double out[11]) {
+// Reductions of a step's partials by one workgroup of FIN_T threads, all
+// eleven quantities in one pass: thread t folds b = t, t + FIN_T, ... in
+// order, then a fixed tree over its wave, then the waves in order.  Bitwise
+// reproducible for a given nb.  Result in thread q < 11: q < 5 the sums and
+// q < 10 the maxima of the nb norm partials, q = 10 the largest of the nl
+// spectral radii.  (One quantity after another, each with a tree of eight
+// barriers over the workgroup, took 10.3 us for a handful of partials and 33 us
+// for 2,816; the bound is the latency of the loads.)
+__device__ double step_reduce(const double* __restrict__ norm_part, const double* __restrict__ lam_part, int nb, int nl,
+                              double (*red)[FIN_W]) {
   double acc[11];
 #pragma unroll
   for (int q = 0; q < 11; ++q) acc[q] = 0.0;
@@ -211,17 +200,15 @@ __device__ void step_reduce(const double* __restrict__ norm_part, const double* 
 #pragma unroll
   for (int q = 0; q < 11; ++q) {
     const double r = q < 5 ? wave_sum(acc[q]) : wave_max(acc[q]);
-    if ((threadIdx.x & 63) == 0) red[q][w] = r;
+    if ((threadIdx.x & 63) == 63) red[q][w] = r;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
+  const int q = threadIdx.x;
+  if (q >= 11) return 0.0;
+  double r = red[q][0];
 #pragma unroll
-    for (int q = 0; q < 11; ++q) {
-      double r = red[q][0];
-      for (int k = 1; k < FIN_W; ++k) r = q < 5 ? r + red[q][k] : max_nan(r, red[q][k]);
-      out[q] = r;
-    }
-  }
+  for (int k = 1; k < FIN_W; ++k) r = q < 5 ? r + red[q][k] : max_nan(r, red[q][k]);
+  return r;
 }
 
 // maximum of nb values, valid in thread 0
@@ -231,7 +218,7 @@ __device__ double block_max(const double* __restrict__ part, int nb, double* red
   for (int b = threadIdx.x; b < nb; b += FIN_T) acc = max_nan(acc, part[b]);
   acc = wave_max(acc);
   __syncthreads();  // red is free
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+  if ((threadIdx.x & 63) == 63) red[threadIdx.x >> 6] = acc;
   __syncthreads();
   double r = red[0];
   for (int k = 1; k < FIN_W; ++k) r = max_nan(r, red[k]);
@@ -261,24 +248,26 @@ __device__ void finalize_step_body(Clock* clk, const double* __restrict__ norm_p
                                    const double* __restrict__ lam_part, int nb, int nl, const StepCtl& ctl,
                                    int* __restrict__ flag, double (*red)[FIN_W]) {
   const int failed = *flag;  // looked at below, so that its load holds the others up no longer
-  double r[11];
-  step_reduce(norm_part, lam_part, nb, nl, red, r);
-  if (threadIdx.x == 0 && !failed) {
-    const double* sums = r;
-    const double* maxs = r + 5;
-    const double lmax = r[10];
-    bool ok = true;
-    for (int v = 0; v < 5; ++v) {
-      clk->rms[v] = sqrt(sums[v] * ctl.inv_n);
-      clk->linf[v] = maxs[v];
-      ok = ok && isfinite(sums[v]) && isfinite(maxs[v]);
-    }
+  const double r = step_reduce(norm_part, lam_part, nb, nl, red);
+  const int q = threadIdx.x;
+  if (q >= 11 || failed) return;
+  // (the eleven threads are lanes of one wave: its ballot needs no barrier)
+  double dt = 0.0;
+  bool ok = isfinite(r);
+  if (q < 5) {
+    clk->rms[q] = sqrt(r * ctl.inv_n);
+  } else if (q < 10) {
+    clk->linf[q - 5] = r;
+  } else {
+    dt = dt_rule(ctl, r);
+    ok = ok && isfinite(dt) && dt > 0.0;
+  }
+  ok = __ballot(!ok) == 0;
+  if (q == 10) {
     clk->t += clk->dt;
     clk->steps += 1;
-    const double dt = dt_rule(ctl, lmax);
-    clk->lam_max = lmax;
+    clk->lam_max = r;
     clk->dt = dt;
-    ok = ok && isfinite(lmax) && isfinite(dt) && dt > 0.0;
     if (!ok) *flag |= 1;
   }
 }
@@ -384,7 +373,7 @@ __device__ inline double node_lambda(const double q[5], const MetView<MET32>& me
 // largest value of a workgroup of 256 threads, to *out
 __device__ inline void block_lambda(double mx, double* red, double* __restrict__ out) {
   mx = wave_max(mx);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
+  if ((threadIdx.x & 63) == 63) red[threadIdx.x >> 6] = mx;
   __syncthreads();
   if (threadIdx.x == 0) *out = max_nan(max_nan(red[0], red[1]), max_nan(red[2], red[3]));
 }
@@ -817,10 +806,8 @@ __global__ __launch_bounds__(FIN_T) void domain_part_reduce_kernel(const DomainS
                                                                    double* __restrict__ part_red) {
   __shared__ double red[11][FIN_W];
   const DomainSub& S = sub[blockIdx.x];
-  double r[11];
-  step_reduce(S.norm_part, S.lam_part, S.nb_tiles, S.nb_tiles, red, r);
-  if (threadIdx.x == 0)
-    for (int q = 0; q < 11; ++q) part_red[11 * blockIdx.x + q] = r[q];
+  const double r = step_reduce(S.norm_part, S.lam_part, S.nb_tiles, S.nb_tiles, red);
+  if (threadIdx.x < 11) part_red[11 * blockIdx.x + threadIdx.x] = r;
 }
 
 // End of a domain step: the first-stage norms over all sub-blocks (their

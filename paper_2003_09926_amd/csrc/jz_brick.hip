@@ -61,16 +61,6 @@ __device__ __forceinline__ void own_pos(int o, int& x, int& y, int& z) {
   z = 2 + (o >> 6);
 }
 
-// Sum and maximum over a wave, in a fixed order.
-__device__ __forceinline__ double wave_sum(double v) {
-  for (int st = 32; st > 0; st >>= 1) v += __shfl_down(v, st);
-  return v;
-}
-__device__ __forceinline__ double wave_max(double v) {
-  for (int st = 32; st > 0; st >>= 1) v = max_nan(v, __shfl_down(v, st));
-  return v;
-}
-
 // MODE bits as in stage_tile: 0 norms, 1 largest spectral radius, 3 keep the
 // double update of the far-field reference planes.
 template <typename Rl, typename TIn, typename TOut, bool MET32, int MODE>
@@ -302,7 +292,7 @@ __global__ __launch_bounds__(NT) void brick_kernel(StageArgs A, const int* __res
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
       const double sv = wave_sum(rs[i]), mv = wave_max(rm[i]);
-      if ((t & 63) == 0) {
+      if ((t & 63) == 63) {
         red[t >> 6][i] = sv;
         red[t >> 6][3 + i] = mv;
       }
@@ -334,7 +324,7 @@ __global__ __launch_bounds__(NT) void brick_kernel(StageArgs A, const int* __res
         lam = lambda_sum(qf, m, J, ph.gamma);
       }
       lam = wave_max(lam);
-      if ((t & 63) == 0) red[t >> 6] = lam;
+      if ((t & 63) == 63) red[t >> 6] = lam;
     }
     __syncthreads();
     if (t == 0) A.lam_part[lt] = max_nan(max_nan(red[0], red[1]), max_nan(red[2], red[3]));

@@ -193,6 +193,38 @@ __host__ __device__ inline int map_index(int i, int n, bool bounded) {
 // NaN-propagating maximum (a plain fmax would drop a NaN).
 __device__ inline double max_nan(double a, double b) { return (b > a || b != b) ? b : a; }
 
+// Sum, and maximum of nonnegative values (or NaN), over the 64 lanes of a wave,
+// all of them active, in a fixed order; valid in the last lane.  Six steps in
+// the vector registers (DPP): within rows of 16 lanes, then the last lane of a
+// row to the next, then that of the lower half to the upper.  (Through
+// __shfl_down, an LDS permutation of two halves a step, ten such reductions
+// took 3 us.)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_or_zero(double v) {
+  const uint64_t b = (uint64_t)__double_as_longlong(v);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, ROWS, 0xf, true);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, ROWS, 0xf, true);
+  return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+}
+__device__ __forceinline__ double wave_sum(double v) {
+  v += dpp_or_zero<0x111, 0xf>(v);  // row_shr 1, 2, 4, 8
+  v += dpp_or_zero<0x112, 0xf>(v);
+  v += dpp_or_zero<0x114, 0xf>(v);
+  v += dpp_or_zero<0x118, 0xf>(v);
+  v += dpp_or_zero<0x142, 0xa>(v);  // row_bcast 15 into rows 1 and 3
+  v += dpp_or_zero<0x143, 0xc>(v);  // row_bcast 31 into rows 2 and 3
+  return v;
+}
+__device__ __forceinline__ double wave_max(double v) {
+  v = max_nan(v, dpp_or_zero<0x111, 0xf>(v));
+  v = max_nan(v, dpp_or_zero<0x112, 0xf>(v));
+  v = max_nan(v, dpp_or_zero<0x114, 0xf>(v));
+  v = max_nan(v, dpp_or_zero<0x118, 0xf>(v));
+  v = max_nan(v, dpp_or_zero<0x142, 0xa>(v));
+  v = max_nan(v, dpp_or_zero<0x143, 0xc>(v));
+  return v;
+}
+
 // FP64 reciprocal and square root for positive, normal arguments: the
 // hardware seed refined to about one ulp.  Reciprocal: with e = 1 - y r the
 // exact value is r / (1 - e) = r (1 + e + e^2 + ...); the second-order step
