@@ -219,8 +219,9 @@ constexpr int lds_pitch() {
 // FAST: exponent 1/2 and 32-bit column offsets (fast_form); the general
 // instantiation takes any block, with the same results.
 // PERSIST: called from the persistent batch kernel's tile loop.
+// flag: where a failed step has left its mark, or NULL if the caller has looked.
 template <typename Rl, typename TIn, typename TOut, bool MET32, int BX, int BY, int MODE, bool FAST, bool PERSIST>
-__device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
+__device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt, const int* __restrict__ flag) {
   constexpr int NT = stage_threads<Rl, BX, BY>();  // threads of the workgroup
   constexpr int TI = BX - 4, TJ = BY - 4;
   constexpr int NI = TI * TJ;                       // owned columns
@@ -296,6 +297,9 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
   static_assert(sizeof(Rl) * (5 * NQB + 10) * NS >= sizeof(double) * 10 * NI, "reduction rows exceed the Q and flux rows");
   double(*sRed)[NI] = reinterpret_cast<double(*)[NI]>(&sQF[0][0]);
 
+  // Looked at behind the first loads, which need not wait for it (64 x 48 x 48
+  // in FP64, 20 launches: 85.8 -> 84.1 us a step).
+  const int failed = flag ? *flag : 0;
   const Phys ph = A.ph;
   const Rl gm1 = (Rl)ph.gm1, gamma = (Rl)ph.gamma;
   const Rl k2 = (Rl)ph.k2, k4 = (Rl)ph.k4;
@@ -481,6 +485,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& A, const int lt) {
     prims_of(Qs, PrM);
     prims_of(Qg, PrC);
   }
+  if (failed) return;  // a failed step froze the state
   // the second-ring column's first gradient plane
   if (hasB) qb_fetch(km);
 
@@ -906,8 +911,7 @@ constexpr int stage_waves_per_eu() {
 template <typename Rl, typename TIn, typename TOut, bool MET32, int BX, int BY, int MODE, bool FAST>
 __global__ __launch_bounds__((stage_threads<Rl, BX, BY>()))
 __attribute__((amdgpu_waves_per_eu(stage_waves_per_eu<Rl, BX, BY, MODE>()))) void stage_kernel(StageArgs A, const int* __restrict__ flag) {
-  if (*flag) return;  // a failed step froze the state
-  stage_tile<Rl, TIn, TOut, MET32, BX, BY, MODE, FAST, false>(A, xcd_remap(blockIdx.x, gridDim.x));
+  stage_tile<Rl, TIn, TOut, MET32, BX, BY, MODE, FAST, false>(A, xcd_remap(blockIdx.x, gridDim.x), flag);
 }
 
 // Many blocks in one persistent launch.  The tiles of all blocks form one
@@ -966,7 +970,7 @@ __attribute__((amdgpu_waves_per_eu(stage_waves_per_eu<Rl, BX, BY, MODE>()))) voi
     A.kchunk = later ? D.kchunk_l : D.kchunk;
     A.in = D.in;
     A.ph = D.ph;
-    stage_tile<Rl, TIn, TOut, MET32, BX, BY, MODE, FAST, true>(A, g - tile_off[a]);
+    stage_tile<Rl, TIn, TOut, MET32, BX, BY, MODE, FAST, true>(A, g - tile_off[a], nullptr);
   }
 }
 
