@@ -12,7 +12,12 @@
 // node by itself, from the one advanced node it goes back to, so that no
 // direction waits for a launch of another.  Measured per stage: the bounded
 // domain of 160 x 112 x 104 nodes 20 us in three launches, 13 us here; the
-// cylindrical mesh of 128 x 64 x 96 nodes 15 us in three, 8 us here.
+// cylindrical mesh of 128 x 64 x 96 nodes 15 us in three, 8 us here.  What
+// bounds it: of the 13 us the launch and the state's reads and writes take 7.5,
+// the metrics (a line of memory a node) and the normals 2.4, the far-field rule
+// 3.4, its power 1.  (A workgroup's slice and direction are scalar and only the
+// direction's metrics are read: 64 x 48 x 48 nodes 0.6 us a launch less than
+// with 64-bit index arithmetic in every thread and all ten metric values.)
 #include <type_traits>
 #include "jz_internal.h"
 
@@ -25,7 +30,7 @@ struct BcArgs {
   int bc[6];             // face types (0 periodic, 1 inflow, 2 far field, 3 centreline)
   double gamma;
   double mach_inf;       // free-stream velocity along x in ambient sound speeds
-  long long end[3];      // threads of the faces of directions <= d
+  int start[9];          // first workgroup of each slice: the xi faces, the four layers of eta, those of zeta
   int axis_blocks;       // workgroups of the centreline, before those of the faces
   const double* ref;     // double states of the reference planes (float stage states), or NULL
   long long ref_off[3];  // offset of each bounded direction's two planes in ref (nodes)
@@ -144,13 +149,15 @@ __device__ void chain_state(const T* __restrict__ q, const MetView<MET32>& met, 
     r[d] = c[d];  // the node this pass sets: back in its layer along d
     const bool lo = c[d] < 2;
     if ((lo ? b.bc[2 * d] : b.bc[2 * d + 1]) == 2) {
-      typename std::conditional<MET32, float, double>::type sm[9];
+      const long long o = node_of(r, b);
+      const auto* __restrict__ sm = met.m + (MET32 ? 9 : 10) * o + 3 * d;
       double J;
-      met.load(node_of(r, b), sm, J);
+      if constexpr (MET32) J = met.jac[o];
+      else J = met.m[10 * o + 9];
       double nh[3], len = 0.0;
 #pragma unroll
       for (int a = 0; a < 3; ++a) {
-        nh[a] = J * (double)(d == 0 ? sm[a] : d == 1 ? sm[3 + a] : sm[6 + a]);  // grad xi_d
+        nh[a] = J * (double)sm[a];  // grad xi_d
         len += nh[a] * nh[a];
       }
       len = sqrt(len);
@@ -236,24 +243,24 @@ __global__ __launch_bounds__(256) void bc_kernel(T* __restrict__ q, const double
     axis_stations<T, MET32>(q, met, b, blockIdx.x, reinterpret_cast<double(*)[5 * AXS]>(axis_buf));
     return;
   }
-  long long t = (long long)(blockIdx.x - b.axis_blocks) * blockDim.x + threadIdx.x;
-  if (t >= b.end[2]) return;
-  const int d = t < b.end[0] ? 0 : t < b.end[1] ? 1 : 2;
-  if (d > 0) t -= b.end[d - 1];
+  // the workgroup's slice, direction and (xi: thread's) layer: scalar arithmetic
+  const int blk = blockIdx.x - b.axis_blocks;
+  int slice = 0, first = 0;
+#pragma unroll
+  for (int i = 1; i < 9; ++i)
+    if (blk >= b.start[i]) {
+      slice = i;
+      first = b.start[i];
+    }
+  const int d = slice == 0 ? 0 : slice < 5 ? 1 : 2;
   // Consecutive threads take neighbouring nodes in memory: along xi (the
   // contiguous index) on the eta and zeta faces, the two adjacent layers of
   // one row on the xi faces.
-  const int ne = b.n[face_e(d)], nf = b.n[face_f(d)];
-  int layer;
-  long long r;
-  if (d == 0) {
-    layer = (int)(t % 4);
-    r = t / 4;
-  } else {
-    const long long face = (long long)ne * nf;
-    layer = (int)(t / face);
-    r = t % face;
-  }
+  const uint32_t t = (uint32_t)(blk - first) * 256u + threadIdx.x;
+  const uint32_t ne = b.n[face_e(d)], nf = b.n[face_f(d)];
+  const int layer = d == 0 ? (int)(t & 3) : (slice - 1) & 3;
+  const uint32_t r = d == 0 ? t >> 2 : t;
+  if (r >= ne * nf) return;
   const int cd = layer < 2 ? layer : b.n[d] - 4 + layer;  // 0, 1, n-2, n-1
   const int ce = (int)(r % ne), cf = (int)(r / ne);
   const int c[3] = {d == 0 ? cd : ce, d == 1 ? cd : d == 0 ? ce : cf, d == 2 ? cd : cf};
@@ -285,18 +292,22 @@ hipError_t launch_bc_typed(T* q, const double* q0, const void* met, const double
   mv.jac = jac;
   BcArgs b;
   ref_layout(n, bnd, b.ref_off);
-  long long count = 0;
+  long long face_blocks = 0;
   for (int d = 0; d < 3; ++d) {
     b.n[d] = n[d];
-    if (bc[2 * d] != 0) count += 4LL * n[(d + 1) % 3] * n[(d + 2) % 3];
-    b.end[d] = count;
+    const long long face = (long long)n[(d + 1) % 3] * n[(d + 2) % 3];
+    if (bc[2 * d] != 0 && 4 * face > 0xffffffffLL) return hipErrorInvalidValue;  // (a block no device holds)
+    for (int l = 0; l < (d == 0 ? 1 : 4); ++l) {
+      b.start[d == 0 ? 0 : 4 * d - 3 + l] = (int)face_blocks;
+      if (bc[2 * d] != 0) face_blocks += ((d == 0 ? 4 * face : face) + 255) / 256;
+    }
   }
   for (int f = 0; f < 6; ++f) b.bc[f] = bc[f];
   b.gamma = gamma;
   b.mach_inf = mach_inf;
   b.ref = ref;
   b.axis_blocks = bc[2] == 3 ? (n[0] + AXS - 1) / AXS : 0;
-  const long long blocks = b.axis_blocks + (count + 255) / 256;
+  const long long blocks = b.axis_blocks + face_blocks;
   if (blocks == 0) return hipSuccess;
   hipLaunchKernelGGL((bc_kernel<T, MET32>), dim3((unsigned)blocks), dim3(256),
                      b.axis_blocks > 0 ? sizeof(double) * AXK * 5 * AXS : 0, st, q, q0, mv, b);
