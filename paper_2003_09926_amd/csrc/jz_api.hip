@@ -5,6 +5,7 @@
 #include <cstdio>
 #include <cstring>
 #include <algorithm>
+#include <chrono>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -51,7 +52,8 @@ hipError_t launch_check_state(const double* q, long long N, double gm1, int* ver
 hipError_t launch_take_state(const double* src, double* q0, long long N, const int* verdict, const void* met,
                              const double* jac, bool met32, int ni, int nj, Interior in, double gamma, double* part,
                              hipStream_t st);
-hipError_t launch_status(const Clock* clk, int* flag, int* verdict, bool reset, Status* out, hipStream_t st);
+hipError_t launch_status(const Clock* clk, int* flag, int* verdict, bool reset, unsigned long long seq, Status* out,
+                         hipStream_t st);
 hipError_t launch_begin(const double* m, const double* q, long long N, void* met, double* jac, double* q0, bool met32,
                         int ni, int nj, Interior in, double gamma, double* part, Clock* clk, int* flag, hipStream_t st);
 hipError_t launch_end(const double* q0, double* q, long long N, const Clock* clk, const int* flag, double* out,
@@ -465,6 +467,7 @@ struct jz_solver {
   double* lam_part;
   Clock* clock;
   int* flag;              // failure flag; flag[1]: verdict on new inputs, 0 between calls
+  unsigned long long answers;  // read_status calls so far
   Status* slot;           // pinned host memory the status kernel answers in (NULL: jz_advance_static)
   bool lam_ready;         // lam_part holds the partials of the current state's first dt
   double* stats;          // sums of u, u^2, p, p^2 per node, or NULL
@@ -694,16 +697,30 @@ int jz_create(int ni, int nj, int nk, const jz_params* p, void* dev_workspace, s
     delete s;
     return fail(JZ_EHIP, "jz_create: %s", hipGetErrorString(e));
   }
+  s->answers = s->slot->seq;  // (the slot may hold the last answer of a solver before this one)
   *out = s;
   return JZ_OK;
 }
 
 // Clock, failure flag and verdict, read once everything queued is done (one
-// kernel and one wait; copies of a few bytes took 35 us each).  reset: new
+// kernel; copies of a few bytes took 35 us each).  The host watches the pinned
+// slot for this call's number, which the kernel writes last, for kWatch; after
+// that, or if the GPU has failed, it waits for the stream.  Measured on an idle
+// stream: 12.9 us a call waiting for the stream, 7.8 us watching.  reset: new
 // inputs, the failure flag starts afresh.
+constexpr std::chrono::microseconds kWatch(2000);
+
 static int read_status(jz_solver* s, bool reset = false) {
-  HIP_TRY(launch_status(s->clock, s->flag, s->flag + 1, reset, s->slot, s->stream));
-  HIP_TRY(hipStreamSynchronize(s->stream));
+  const unsigned long long seq = ++s->answers;
+  HIP_TRY(launch_status(s->clock, s->flag, s->flag + 1, reset, seq, s->slot, s->stream));
+  const auto t0 = std::chrono::steady_clock::now();
+  for (int n = 0; __atomic_load_n(&s->slot->seq, __ATOMIC_ACQUIRE) != seq; ++n) {
+    __builtin_ia32_pause();
+    if ((n & 63) == 63 && std::chrono::steady_clock::now() - t0 > kWatch) {
+      HIP_TRY(hipStreamSynchronize(s->stream));
+      break;
+    }
+  }
   return JZ_OK;
 }
 
@@ -1000,10 +1017,14 @@ int jz_get_state(jz_solver* s, double* q, int on_device) {
   if (!s->state_set) return fail(JZ_ESTATE, "jz_get_state: no state set");
   // straight into the caller's device buffer where a kernel can write it
   const bool direct = on_device && direct_access(q, s->device);
-  HIP_TRY(launch_nodes_to_soa(s->q0, direct ? q : s->qa, s->N, 5, s->flag, s->slot, s->stream));
-  if (!direct)
-    HIP_TRY(hipMemcpyAsync(q, s->qa, 5 * s->N * sizeof(double),
-                           on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s->stream));
+  if (direct) {
+    HIP_TRY(launch_nodes_to_soa(s->q0, q, s->N, 5, nullptr, nullptr, s->stream));
+    const int rc = read_status(s);
+    return rc ? rc : health(s);
+  }
+  HIP_TRY(launch_nodes_to_soa(s->q0, s->qa, s->N, 5, s->flag, s->slot, s->stream));
+  HIP_TRY(hipMemcpyAsync(q, s->qa, 5 * s->N * sizeof(double),
+                         on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s->stream));
   HIP_TRY(hipStreamSynchronize(s->stream));
   return health(s);
 }

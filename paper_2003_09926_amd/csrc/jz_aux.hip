@@ -425,13 +425,14 @@ __global__ __launch_bounds__(TR_T) void take_state_kernel(const double* __restri
 // slot.  reset: the inputs were new, so the flag starts afresh; the verdict is
 // always left at 0 for the next check.
 __global__ void status_kernel(const Clock* __restrict__ clk, int* __restrict__ flag, int* __restrict__ verdict, int reset,
-                              Status* __restrict__ out) {
+                              unsigned long long seq, Status* __restrict__ out) {
   if (threadIdx.x != 0) return;
   out->clock = *clk;
   out->verdict = *verdict;
   *verdict = 0;
   if (reset) *flag = 0;
   out->flag = reset ? 0 : *flag;
+  __hip_atomic_store(&out->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // First launch of a run in the caller's buffers: metrics and state into the
@@ -624,8 +625,9 @@ hipError_t launch_take_state(const double* src, double* q0, long long N, const i
   return hipGetLastError();
 }
 
-hipError_t launch_status(const Clock* clk, int* flag, int* verdict, bool reset, Status* out, hipStream_t st) {
-  hipLaunchKernelGGL(status_kernel, dim3(1), dim3(64), 0, st, clk, flag, verdict, reset ? 1 : 0, out);
+hipError_t launch_status(const Clock* clk, int* flag, int* verdict, bool reset, unsigned long long seq, Status* out,
+                         hipStream_t st) {
+  hipLaunchKernelGGL(status_kernel, dim3(1), dim3(64), 0, st, clk, flag, verdict, reset ? 1 : 0, seq, out);
   return hipGetLastError();
 }
 

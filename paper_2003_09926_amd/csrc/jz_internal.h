@@ -42,11 +42,13 @@ struct Clock {
 };
 
 // What a call that answers the host leaves in the solver's pinned slot: the
-// clock, the failure flag and the verdict on the last inputs checked.
+// clock, the failure flag and the verdict on the last inputs checked.  The host
+// watches for the answer's number (see await_status).
 struct Status {
   Clock clock;
   int flag;
   int verdict;
+  unsigned long long seq;  // number of the answer, written last
 };
 
 // Per-step reduction settings read by the finalize kernels.

@@ -119,3 +119,21 @@ def test_many_solvers_share_the_answer_pages(B):
         assert n == 1 and t == dt == 1e-4 * (k + 1)
     for s in ss:
         s.close()
+
+
+def test_answers_are_those_of_the_call(B):
+    """The host watches a pinned slot for the number of its answer: solvers one
+    after another in the same slot, answers of short and long queues."""
+    print("[gpu-case] answers through reused slots", flush=True)
+    dims = (96, 64, 40)
+    g, q = I.jet_box_case(dims, seed=2)
+    for steps in (1, 3, 2, 60):
+        with B.Solver(dims, B.params_default()) as s:
+            s.set_grid_metrics(g.metrics)
+            s.set_state(q)
+            t = [s.clock()[2]]
+            for n in (steps, 1):
+                s.advance(n)
+                t.append(s.clock()[2])
+            assert t == [0, steps, steps + 1]
+            assert np.isfinite(s.residual_norms()[0]).all()
