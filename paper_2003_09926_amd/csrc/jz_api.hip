@@ -18,7 +18,7 @@ hipError_t launch_stage_fp64(const StageArgs& a, const int* flag, int mode, int 
                              hipStream_t st);
 hipError_t launch_stage_fp32(const StageArgs& a, const int* flag, int kind, int bx, int by, int nblocks,
                              hipStream_t st);
-hipError_t launch_brick(const StageArgs& a, bool f32, const int* flag, int stage, bool last, int nbricks,
+hipError_t launch_brick(const StageArgs& a, bool f32, const int* flag, int stage, bool last, bool small, int nbricks,
                         hipStream_t st);
 bool stage_shape_supported(int bx, int by);
 bool stage32_shape_supported(int bx, int by);
@@ -270,27 +270,38 @@ int partial_capacity(int ni, int nj, int nk, const Tiling& t, int own) {
 }
 
 // Bricks a block is advanced in when the launch shape is left to the library
-// (0: it marches, see jz_brick.hip).  The bricks take about as many rounds as
-// there are bricks per workgroup slot, the march of a block this small the
-// time of six or so planes in turn (own_kchunk).  Measured steps, bricks /
-// march: FP64 (one brick per CU, 256 a round) 45 bricks (24 x 20 x 18) 46 /
-// 86 us, 245 (48 x 40 x 28) 51 / 89, 288 (48 x 48 x 32) 84 / 79, 576 117 / 92;
-// FP32-flux (two per CU) 45 bricks 38 / 86 us, 1024 88 / 91, 1280 108 / 119,
-// 1408 123 / 119, 1536 127 / 120.
-constexpr int kMaxBricks64 = 256, kMaxBricks32 = 1280;
+// (see jz_brick.hip).  They take about as many rounds as there are bricks per
+// workgroup slot, the march of a block this small the time of six or so planes
+// in turn (own_kchunk).  Measured steps, small / wide bricks: FP64 (two small
+// ones per CU) 240 small bricks (32 x 24 x 20) 36.5 / 44.2 us, 441 44 / 46, 640
+// 59 / 46; FP32-flux 300 36.6 / 37.8, 441 37 / 38, 640 40.2 / 38.2.  Wide bricks
+// / march: FP64 (one brick per CU, 256 a round) 245 wide bricks (48 x 40 x 28)
+// 51 / 89 us, 288 (48 x 48 x 32) 84 / 79, 576 117 / 92; FP32-flux (two per CU)
+// 1024 88 / 91, 1280 108 / 119, 1408 123 / 119, 1536 127 / 120.
+constexpr int kMaxSmall = 512, kMaxBricks64 = 256, kMaxBricks32 = 1280;
 
-int brick_count(int ni, int nj, int nk, const jz_params* p, int n[2] = nullptr) {
-  if (p && (p->tile_i > 0 || p->kchunk > 0 || p->n_stages < 2 || p->tv_alpha != 0.5)) return 0;
+struct Bricks {
+  int count, n[2];  // bricks of the block (0: it marches), those along xi and eta
+  bool small;
+};
+
+Bricks bricks_of(int ni, int nj, int nk, const jz_params* p) {
+  Bricks b{0, {0, 0}, false};
+  if (p && (p->tile_i > 0 || p->kchunk > 0 || p->n_stages < 2 || p->tv_alpha != 0.5)) return b;
   const Interior in = interior_of(ni, nj, nk, p);
-  const long long bi = (in.hi[0] - in.lo[0] + kBrickI - 1) / kBrickI, bj = (in.hi[1] - in.lo[1] + kBrickJ - 1) / kBrickJ,
-                  bk = (in.hi[2] - in.lo[2] + kBrickK - 1) / kBrickK;
-  const long long most = p && p->precision == JZ_FP32_FLUX ? kMaxBricks32 : kMaxBricks64;
-  if (bi > most || bj > most || bk > most || bi * bj * bk > most) return 0;
-  if (n) {
-    n[0] = (int)bi;
-    n[1] = (int)bj;
-  }
-  return (int)(bi * bj * bk);
+  const bool f32 = p && p->precision == JZ_FP32_FLUX;
+  auto fit = [&](int si, int sj, int sk, long long most) {
+    const long long bi = (in.hi[0] - in.lo[0] + si - 1) / si, bj = (in.hi[1] - in.lo[1] + sj - 1) / sj,
+                    bk = (in.hi[2] - in.lo[2] + sk - 1) / sk;
+    if (bi > most || bj > most || bk > most || bi * bj * bk > most) return false;
+    b.count = (int)(bi * bj * bk);
+    b.n[0] = (int)bi;
+    b.n[1] = (int)bj;
+    return true;
+  };
+  b.small = fit(kSmallBrick, kSmallBrick, kSmallBrick, kMaxSmall);
+  if (!b.small) fit(kBrickI, kBrickJ, kBrickK, f32 ? kMaxBricks32 : kMaxBricks64);
+  return b;
 }
 
 // Partial sums to have room for where the launch shape is left to the library:
@@ -300,7 +311,7 @@ constexpr int kOwnTiles = 512;
 
 int own_parts(int ni, int nj, int nk, const jz_params* p) {
   if (p->tile_i > 0 || p->kchunk > 0) return 0;
-  return std::max(brick_count(ni, nj, nk, p), kOwnTiles);
+  return std::max(bricks_of(ni, nj, nk, p).count, kOwnTiles);
 }
 
 Layout layout_for(long long N, const Tiling& t, int prec, int cap, bool stats, long long ref_nodes) {
@@ -446,7 +457,7 @@ struct jz_solver {
   Phys ph;
   Tiling tl;
   int own_kc;               // planes per chunk of the tiles (tl) it marches in by itself
-  int nbricks, brick_n[2];  // bricks it advances in instead (along xi, eta), or 0
+  Bricks bricks;            // bricks it advances in instead
   Interior in;      // nodes the residual advances
   int cap;          // tiles the partial-sum arrays can hold
   Layout L;
@@ -508,7 +519,7 @@ void setup_shape(jz_solver* s, int ni, int nj, int nk, const jz_params* p, bool 
   pick_tiling_for_device(ni, nj, nk, p, &s->tl);
   s->in = interior_of(ni, nj, nk, p);
   s->prec = p->precision;
-  s->nbricks = room ? brick_count(ni, nj, nk, p, s->brick_n) : 0;
+  s->bricks = room ? bricks_of(ni, nj, nk, p) : Bricks{0, {0, 0}, false};
   s->cap = partial_capacity(ni, nj, nk, s->tl, room ? own_parts(ni, nj, nk, p) : 0);
   pick_own_chunk(s);
   s->L = layout_for(s->N, s->tl, s->prec, s->cap, p->stats_interval > 0,
@@ -965,10 +976,10 @@ static int advance_steps(jz_solver* s, int nsteps) {
         if (rc_ev) return rc_ev;
         HIP_TRY(hipEventRecord(e0, s->stream));
       }
-      if (s->nbricks > 0) {
-        a.tiles_i = s->brick_n[0];
-        a.tiles_j = s->brick_n[1];
-        HIP_TRY(launch_brick(a, s->prec == JZ_FP32_FLUX, s->flag, k, last, s->nbricks, s->stream));
+      if (s->bricks.count > 0) {
+        a.tiles_i = s->bricks.n[0];
+        a.tiles_j = s->bricks.n[1];
+        HIP_TRY(launch_brick(a, s->prec == JZ_FP32_FLUX, s->flag, k, last, s->bricks.small, s->bricks.count, s->stream));
       } else {
         a.kchunk = s->own_kc;
         a.nchunks = own_chunks;
@@ -989,7 +1000,7 @@ static int advance_steps(jz_solver* s, int nsteps) {
         HIP_TRY(hipMemcpyAsync(s->q0, s->qa, 5 * s->N * sizeof(double), hipMemcpyDeviceToDevice, s->stream));
       in = out;
     }
-    const int parts = s->nbricks > 0 ? s->nbricks : s->tl.tiles_i * s->tl.tiles_j * own_chunks;
+    const int parts = s->bricks.count > 0 ? s->bricks.count : s->tl.tiles_i * s->tl.tiles_j * own_chunks;
     HIP_TRY(launch_finalize_step(s->clock, s->norm_part, s->lam_part, parts, step_ctl(s), s->flag,
                                  s->stream));
     if (s->stats && ++s->stat_steps % s->p.stats_interval == 0) {
@@ -1211,8 +1222,8 @@ int jz_set_tiling(jz_solver* s, int tile_i, int tile_j, int kchunk) {
   s->tl = t;
   // back to the library's choice: bricks, if the partial sums have room for them
   pick_own_chunk(s);
-  s->nbricks = brick_count(s->ni, s->nj, s->nk, &p, s->brick_n);
-  if (s->nbricks > s->cap) s->nbricks = 0;
+  s->bricks = bricks_of(s->ni, s->nj, s->nk, &p);
+  if (s->bricks.count > s->cap) s->bricks.count = 0;
   return JZ_OK;
 }
 
@@ -1987,10 +1998,11 @@ int jz_batch_autotune(jz_batch* b, int trial_steps, const char* cache_path, int*
   struct Shape {
     jz_params p;
     Tiling tl;
-    int own_kc, nbricks;
+    int own_kc;
+    Bricks bricks;
   };
   std::vector<Shape> old;
-  for (jz_solver* s : b->m) old.push_back({s->p, s->tl, s->own_kc, s->nbricks});
+  for (jz_solver* s : b->m) old.push_back({s->p, s->tl, s->own_kc, s->bricks});
   for (size_t i = 0; i < b->m.size(); ++i) {
     int rc = jz_set_tiling(b->m[i], best_ti, best_tj, best_kc);
     if (rc) {
@@ -1998,7 +2010,7 @@ int jz_batch_autotune(jz_batch* b, int trial_steps, const char* cache_path, int*
         b->m[j]->p = old[j].p;
         b->m[j]->tl = old[j].tl;
         b->m[j]->own_kc = old[j].own_kc;
-        b->m[j]->nbricks = old[j].nbricks;
+        b->m[j]->bricks = old[j].bricks;
       }
       return rc;
     }

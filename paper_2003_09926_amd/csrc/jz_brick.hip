@@ -3,22 +3,23 @@
 // The marching stage kernel (jz_stage_kernel.h) walks the planes of a chunk
 // one after another, about 2.2 us a plane, with some four planes' worth of
 // warm-up and set-up: 14 us a stage even for chunks of one plane.  Here a
-// workgroup takes a brick of 8 x 8 x 4 owned nodes and computes every flux it
-// needs at once, one node per thread: the 256 owned nodes and the 256 nodes
-// next to its faces (twice the flux work per owned node).
-//   phase 1  every thread loads its node (Q, metrics) and, for 336 of them,
-//            a second one that only supplies primitives and Q (the second
-//            ring, and the first ring's edges); primitives and Q to LDS
+// workgroup takes a brick of owned nodes and computes every flux it needs at
+// once, one node per thread: its own and those next to its faces.
+//   phase 1  every thread loads its node (Q, metrics) and some a second one
+//            that only supplies primitives and Q (the second ring, and the
+//            first ring's edges); primitives and Q to LDS
 //   phase 2  fluxes, dissipation scales and sensors of the thread's node; a
 //            halo node keeps those of its face's direction only
-//   phase 3  residual and update: the owner of a node takes two of the five
-//            variables, the thread 256 above it three
-// Measured, the step of a 24 x 20 x 18 block: FP64 86 us marching, 46 us in
-// bricks, FP32-flux 86 and 38 us (48 x 40 x 28 FP64: 89 and 51 us, 48 x 48 x 48
-// FP32-flux: 89 and 53 us).
-// What bounds it: for the smallest blocks the chain of the three phases in
-// one workgroup (two waves per SIMD, one workgroup per CU in FP64), for larger
-// ones the doubled flux work, which is why large blocks march.
+//   phase 3  residual and update, the variables of an owned node shared out
+//            among threads
+// Wide bricks, 8 x 8 x 4 nodes and 512 threads, have as many halo nodes as
+// owned ones (twice the flux work per owned node); small ones, 4 x 4 x 4 nodes
+// and a wave on each SIMD, 2.5 times the work, but a block of few nodes is on
+// more CUs with half as many waves to a SIMD in turn.  Measured steps,
+// march / wide / small bricks: FP64 24 x 20 x 18 86 / 44 / 35 us, 48 x 40 x 28
+// 89 / 48 / 72; FP32-flux 24 x 20 x 18 86 / 37 / 33, 48 x 48 x 48 89 / 50 / 62.
+// What bounds them: the chain of the three phases in one workgroup, for larger
+// blocks the extra flux work, which is why those march.
 // The arithmetic of a node is the marching kernel's (jz_node.h, and the same
 // order of operations here), so the states are bitwise the same.
 #include "jz_node.h"
@@ -27,13 +28,128 @@ namespace jz {
 
 namespace {
 
-constexpr int BI = kBrickI, BJ = kBrickJ, BK = kBrickK;   // owned nodes
-constexpr int SX = BI + 4, SY = BJ + 4, SZ = BK + 4;      // with the two-node halo
-constexpr int NS = SX * SY * SZ;
-constexpr int NOWN = BI * BJ * BK;
-constexpr int NT = 2 * NOWN;
-static_assert(BI == 8 && BJ == 8 && BK == 4, "the thread roles below are for 8 x 8 x 4 bricks");
-static_assert(2 * (BJ * BK + BI * BK + BI * BJ) == NOWN, "one halo thread per owned node");
+// The threads of a brick.  Each has up to two nodes: (x, y, z), counted with
+// the two-node halo, whose fluxes it computes in direction dir (-1: all three,
+// an owned node; 3: none), and with `two` (x2, y2, z2), which it only supplies.
+struct Roles {
+  int dir, x, y, z, x2, y2, z2;
+  bool one, two;
+};
+
+// 8 x 8 x 4 owned nodes, 512 threads: the upper half takes the halo nodes, and
+// in phase 3 three of the five variables of the owned nodes 256 below.
+struct WideBrick {
+  static constexpr int BI = kBrickI, BJ = kBrickJ, BK = kBrickK;
+  static constexpr int NOWN = BI * BJ * BK, NT = 2 * NOWN;
+  static_assert(BI == 8 && BJ == 8 && BK == 4, "the roles below are for 8 x 8 x 4 bricks");
+  static_assert(2 * (BJ * BK + BI * BK + BI * BJ) == NOWN, "one halo thread per owned node");
+  // owned node of thread t in phase 3, and its variables [v0, v0 + nv)
+  static __device__ __forceinline__ int own(int t) { return t & (NOWN - 1); }
+  static __device__ __forceinline__ int v0(int t) { return t < NOWN ? 0 : 2; }
+  static __device__ __forceinline__ int nv(int t) { return t < NOWN ? 2 : 3; }
+  static constexpr int NV = 3;
+  // Position of owned node o.  The rows of a 16-lane group are two apart, so
+  // that with 12-slot rows its 64-bit LDS accesses fall into 16 banks.
+  static __device__ __forceinline__ void own_pos(int o, int& x, int& y, int& z) {
+    const int g = (o >> 3) & 7;
+    x = 2 + (o & 7);
+    y = 2 + ((g & 4) | ((g & 1) << 1) | ((g >> 1) & 1));
+    z = 2 + (o >> 6);
+  }
+  static __device__ __forceinline__ Roles roles(int t) {
+    Roles r;
+    const int o = own(t);
+    r.one = true;
+    if (t < NOWN) {
+      r.dir = -1;
+      own_pos(o, r.x, r.y, r.z);
+      // edges of the first ring: along zeta 16, eta 32, xi 32
+      r.two = t < 80;
+      const int e = t < 16 ? t : t < 48 ? t - 16 : t - 48;
+      const int a = (e & 1), b = (e >> 1) & 1, c = e >> 2;
+      r.x2 = t < 48 ? (a ? BI + 2 : 1) : 2 + c;
+      r.y2 = t < 16 ? (b ? BJ + 2 : 1) : t < 48 ? 2 + c : (a ? BJ + 2 : 1);
+      r.z2 = t < 16 ? 2 + c : (b ? BK + 2 : 1);
+      return r;
+    }
+    r.two = true;
+    r.dir = o < 64 ? 0 : o < 128 ? 1 : 2;
+    if (r.dir == 0) {
+      const int hi = o >> 5;
+      r.y = r.y2 = 2 + (o & 7);
+      r.z = r.z2 = 2 + ((o >> 3) & 3);
+      r.x = hi ? BI + 2 : 1;
+      r.x2 = hi ? BI + 3 : 0;
+    } else if (r.dir == 1) {
+      const int hi = (o - 64) >> 5;
+      r.x = r.x2 = 2 + (o & 7);
+      r.z = r.z2 = 2 + ((o >> 3) & 3);
+      r.y = hi ? BJ + 2 : 1;
+      r.y2 = hi ? BJ + 3 : 0;
+    } else {
+      const int hi = (o - 128) >> 6;
+      r.x = r.x2 = 2 + (o & 7);
+      r.y = r.y2 = 2 + ((o >> 3) & 7);
+      r.z = hi ? BK + 2 : 1;
+      r.z2 = hi ? BK + 3 : 0;
+    }
+    return r;
+  }
+};
+
+// 4 x 4 x 4 owned nodes, a wave on each SIMD: the first takes the owned nodes,
+// the others the halo nodes of a direction each (lanes 0..31) and 16 edges of
+// the first ring along that direction (lanes 32..47).  In phase 3 the waves
+// take the variables of the owned nodes, the last wave two.
+struct SmallBrick {
+  static constexpr int BI = kSmallBrick, BJ = kSmallBrick, BK = kSmallBrick;
+  static constexpr int NOWN = BI * BJ * BK, NT = 4 * NOWN;
+  static_assert(NOWN == 64, "one owned node per lane");
+  static __device__ __forceinline__ int own(int t) { return t & 63; }
+  static __device__ __forceinline__ int v0(int t) { return t >> 6; }
+  static __device__ __forceinline__ int nv(int t) { return t < 192 ? 1 : 2; }
+  static constexpr int NV = 2;
+  static __device__ __forceinline__ void own_pos(int o, int& x, int& y, int& z) {
+    x = 2 + (o & 3);
+    y = 2 + ((o >> 2) & 3);
+    z = 2 + (o >> 4);
+  }
+  static __device__ __forceinline__ Roles roles(int t) {
+    Roles r;
+    const int l = t & 63, d = (t >> 6) - 1;
+    r.one = true;
+    r.two = false;
+    r.x2 = r.y2 = r.z2 = 2;
+    if (d < 0) {
+      r.dir = -1;
+      own_pos(l, r.x, r.y, r.z);
+      return r;
+    }
+    int p[3], p2[3];  // along the wave's direction d, and the two others (e before f)
+    if (l < 32) {
+      const int hi = l >> 4;
+      p[0] = hi ? BI + 2 : 1;
+      p2[0] = hi ? BI + 3 : 0;
+      p[1] = p2[1] = 2 + (l & 3);
+      p[2] = p2[2] = 2 + ((l >> 2) & 3);
+      r.dir = d;
+      r.two = true;
+    } else {
+      p[0] = p2[0] = 2 + (l & 3);
+      p[1] = p2[1] = (l & 4) ? BI + 2 : 1;
+      p[2] = p2[2] = (l & 8) ? BI + 2 : 1;
+      r.dir = 3;
+      r.one = l < 48;
+    }
+    r.x = d == 0 ? p[0] : p[1];
+    r.y = d == 1 ? p[0] : d == 0 ? p[1] : p[2];
+    r.z = d == 2 ? p[0] : p[2];
+    r.x2 = d == 0 ? p2[0] : p2[1];
+    r.y2 = d == 1 ? p2[0] : d == 0 ? p2[1] : p2[2];
+    r.z2 = d == 2 ? p2[0] : p2[2];
+    return r;
+  }
+};
 
 // A value the compiler cannot trace to its expression: multiplications and
 // additions on either side of it are not contracted, as where the marching
@@ -44,27 +160,20 @@ __device__ __forceinline__ T opaque(T x) {
   return x;
 }
 
-// Slots of a node (x, y, z counted with the halo) in the rows of the fluxes,
-// scales and sensors along each direction: owned nodes and that direction's
-// two halo layers.
-__device__ __forceinline__ int slot_x(int x, int y, int z) { return (x - 1) + (BI + 2) * ((y - 2) + BJ * (z - 2)); }
-__device__ __forceinline__ int slot_y(int x, int y, int z) { return (x - 2) + BI * ((y - 1) + (BJ + 2) * (z - 2)); }
-__device__ __forceinline__ int slot_z(int x, int y, int z) { return (x - 2) + BI * ((y - 2) + BJ * (z - 1)); }
-constexpr int NX = (BI + 2) * BJ * BK, NY = BI * (BJ + 2) * BK, NZ = BI * BJ * (BK + 2);
-
-// Position of owned thread o.  The rows of a 16-lane group are two apart, so
-// that with 12-slot rows its 64-bit LDS accesses fall into 16 banks.
-__device__ __forceinline__ void own_pos(int o, int& x, int& y, int& z) {
-  const int g = (o >> 3) & 7;
-  x = 2 + (o & 7);
-  y = 2 + ((g & 4) | ((g & 1) << 1) | ((g >> 1) & 1));
-  z = 2 + (o >> 6);
-}
-
 // MODE bits as in stage_tile: 0 norms, 1 largest spectral radius, 3 keep the
 // double update of the far-field reference planes.
-template <typename Rl, typename TIn, typename TOut, bool MET32, int MODE>
-__global__ __launch_bounds__(NT) void brick_kernel(StageArgs A, const int* __restrict__ flag) {
+template <typename S, typename Rl, typename TIn, typename TOut, bool MET32, int MODE>
+__global__ __launch_bounds__(S::NT) __attribute__((amdgpu_waves_per_eu(2))) void brick_kernel(StageArgs A, const int* __restrict__ flag) {
+  constexpr int BI = S::BI, BJ = S::BJ, BK = S::BK, NOWN = S::NOWN;
+  constexpr int SX = BI + 4, SY = BJ + 4, SZ = BK + 4;      // with the two-node halo
+  constexpr int NS = SX * SY * SZ;
+  constexpr int NX = (BI + 2) * BJ * BK, NY = BI * (BJ + 2) * BK, NZ = BI * BJ * (BK + 2);
+  // Slots of a node (x, y, z counted with the halo) in the rows of the fluxes,
+  // scales and sensors along each direction: owned nodes and that direction's
+  // two halo layers.
+  auto slot_x = [](int x, int y, int z) { return (x - 1) + (BI + 2) * ((y - 2) + BJ * (z - 2)); };
+  auto slot_y = [](int x, int y, int z) { return (x - 2) + BI * ((y - 1) + (BJ + 2) * (z - 2)); };
+  auto slot_z = [](int x, int y, int z) { return (x - 2) + BI * ((y - 2) + BJ * (z - 1)); };
   constexpr bool NORMS = (MODE & 1) != 0;
   constexpr bool LAMMAX = (MODE & 2) != 0;
   constexpr bool KEEP_REF = (MODE & 8) != 0;
@@ -87,41 +196,14 @@ __global__ __launch_bounds__(NT) void brick_kernel(StageArgs A, const int* __res
               : t < SX + SY   ? map_index(j0 - 2 + t - SX, A.nj, A.in.bnd & 2)
                               : map_index(k0 - 2 + t - SX - SY, A.nk, A.in.bnd & 4);
   }
-  // the thread's flux node, and the node (x2, y2, z2) it also supplies
-  const bool owner = t < NOWN;
-  const int o = owner ? t : t - NOWN;
-  int xo, yo, zo;                 // owned node this thread (or its lower half) updates
-  own_pos(o, xo, yo, zo);
-  int x = xo, y = yo, z = zo, x2, y2, z2;
-  const int dir = owner ? -1 : o < 64 ? 0 : o < 128 ? 1 : 2;
-  const int wdir = __builtin_amdgcn_readfirstlane(dir);  // (the same for a whole wave)
-  if (dir < 0) {
-    // edges of the first ring: along zeta 16, eta 32, xi 32
-    const int e = t < 16 ? t : t < 48 ? t - 16 : t - 48;
-    const int a = (e & 1), b = (e >> 1) & 1, c = e >> 2;
-    x2 = t < 48 ? (a ? BI + 2 : 1) : 2 + c;
-    y2 = t < 16 ? (b ? BJ + 2 : 1) : t < 48 ? 2 + c : (a ? BJ + 2 : 1);
-    z2 = t < 16 ? 2 + c : (b ? BK + 2 : 1);
-  } else if (dir == 0) {
-    const int hi = o >> 5;
-    y = y2 = 2 + (o & 7);
-    z = z2 = 2 + ((o >> 3) & 3);
-    x = hi ? BI + 2 : 1;
-    x2 = hi ? BI + 3 : 0;
-  } else if (dir == 1) {
-    const int hi = (o - 64) >> 5;
-    x = x2 = 2 + (o & 7);
-    z = z2 = 2 + ((o >> 3) & 3);
-    y = hi ? BJ + 2 : 1;
-    y2 = hi ? BJ + 3 : 0;
-  } else {
-    const int hi = (o - 128) >> 6;
-    x = x2 = 2 + (o & 7);
-    y = y2 = 2 + ((o >> 3) & 7);
-    z = hi ? BK + 2 : 1;
-    z2 = hi ? BK + 3 : 0;
-  }
-  const bool two = !owner || t < 80;
+  const Roles ro = S::roles(t);
+  const int x = ro.x, y = ro.y, z = ro.z, dir = ro.dir;
+  const bool owner = t < NOWN, two = ro.two;
+  // (a wave's lanes with fluxes have them in the same direction)
+  const int wdir = __builtin_amdgcn_readfirstlane(dir);
+  const int o = S::own(t);
+  int xo, yo, zo;                 // owned node this thread updates variables of
+  S::own_pos(o, xo, yo, zo);
   __syncthreads();
 
   // ---- phase 1: loads, primitives ------------------------------------------
@@ -135,7 +217,7 @@ __global__ __launch_bounds__(NT) void brick_kernel(StageArgs A, const int* __res
 #pragma unroll
   for (int v = 0; v < 5; ++v) Q[v] = (Rl)qin[5 * n1 + v];
   if (two) {
-    const long long n2 = node(x2, y2, z2);
+    const long long n2 = node(ro.x2, ro.y2, ro.z2);
 #pragma unroll
     for (int v = 0; v < 5; ++v) Q2[v] = (Rl)qin[5 * n2 + v];
   }
@@ -144,11 +226,11 @@ __global__ __launch_bounds__(NT) void brick_kernel(StageArgs A, const int* __res
   met.jac = A.jac;
   met.load(n1, m, Jg);
   // the variables this thread updates, and their Q(0)
-  const int v0 = owner ? 0 : 2, nv = owner ? 2 : 3;
-  double q0v[3];
+  const int v0 = S::v0(t), nv = S::nv(t);
+  double q0v[S::NV];
   if constexpr (!Q0_IN_LDS) {
 #pragma unroll
-    for (int i = 0; i < 3; ++i)
+    for (int i = 0; i < S::NV; ++i)
       if (i < nv) q0v[i] = A.q0[5 * no + v0 + i];
   }
   const double adt = A.alpha * A.clock->dt;
@@ -161,14 +243,16 @@ __global__ __launch_bounds__(NT) void brick_kernel(StageArgs A, const int* __res
     ctr[2] = opaque(p.w);
     ctr[3] = opaque(p.T);
     ctr[4] = opaque(p.p);
+    if (ro.one) {
 #pragma unroll
-    for (int k = 0; k < 5; ++k) {
-      sPr[k][c] = ctr[k];
-      sQ[k][c] = Q[k];
+      for (int k = 0; k < 5; ++k) {
+        sPr[k][c] = ctr[k];
+        sQ[k][c] = Q[k];
+      }
     }
   }
   if (two) {
-    const int c2 = x2 + SX * (y2 + SY * z2);
+    const int c2 = ro.x2 + SX * (ro.y2 + SY * ro.z2);
     const Prim<Rl> p = primitives(Q2, gm1, gamma);
     const Rl pr[5] = {p.u, p.v, p.w, p.T, p.p};
 #pragma unroll
@@ -180,7 +264,7 @@ __global__ __launch_bounds__(NT) void brick_kernel(StageArgs A, const int* __res
   __syncthreads();
 
   // ---- phase 2: fluxes, scales, sensors --------------------------------------
-  {
+  if (dir < 3) {
     Rl nxm[5], nxp[5], nym[5], nyp[5], nzm[5], nzp[5];
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
@@ -228,7 +312,9 @@ __global__ __launch_bounds__(NT) void brick_kernel(StageArgs A, const int* __res
   constexpr int DX = 1, DY = BI, DZ = BI * BJ;   // neighbours in the flux rows
   const bool mine = i0 + xo - 2 < A.in.hi[0] && j0 + yo - 2 < A.in.hi[1] && k0 + zo - 2 < A.in.hi[2];
   const double J = sJ[o];
-  double qn[3] = {0, 0, 0}, rs[3] = {0, 0, 0}, rm[3] = {0, 0, 0};
+  double qn[S::NV], rs[S::NV], rm[S::NV];
+#pragma unroll
+  for (int i = 0; i < S::NV; ++i) qn[i] = rs[i] = rm[i] = 0.0;
   {
     Rl e2xp, e4xp, sgxp, e2xm, e4xm, sgxm, e2yp, e4yp, sgyp, e2ym, e4ym, sgym, e2zp, e4zp, sgzp, e2zm, e4zm, sgzm;
     face_coefs(k2, k4, sFx[6][qx], sFx[6][qx + DX], sFx[5][qx], sFx[5][qx + DX], e2xp, e4xp, sgxp);
@@ -238,7 +324,7 @@ __global__ __launch_bounds__(NT) void brick_kernel(StageArgs A, const int* __res
     face_coefs(k2, k4, sFz[6][qz], sFz[6][qz + DZ], sFz[5][qz], sFz[5][qz + DZ], e2zp, e4zp, sgzp);
     face_coefs(k2, k4, sFz[6][qz - DZ], sFz[6][qz], sFz[5][qz - DZ], sFz[5][qz], e2zm, e4zm, sgzm);
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
+    for (int i = 0; i < S::NV; ++i) {
       if (i >= nv) break;
       const int v = v0 + i;
       const Rl* q = &sQ[v][co];
@@ -286,71 +372,85 @@ __global__ __launch_bounds__(NT) void brick_kernel(StageArgs A, const int* __res
     }
   }
 
-  // ---- fixed-order reductions over the brick --------------------------------
+  // ---- fixed-order reductions over the brick: the waves of a variable in
+  // turn (a small brick has one) ----------------------------------------------
+  constexpr int WV = NOWN / 64;
   if constexpr (NORMS) {
-    double(*red)[6] = reinterpret_cast<double(*)[6]>(&sPr[0][0]);  // a row per wave
+    double(*red)[2 * S::NV] = reinterpret_cast<double(*)[2 * S::NV]>(&sPr[0][0]);  // a row per wave
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
+    for (int i = 0; i < S::NV; ++i) {
       const double sv = wave_sum(rs[i]), mv = wave_max(rm[i]);
       if ((t & 63) == 63) {
         red[t >> 6][i] = sv;
-        red[t >> 6][3 + i] = mv;
+        red[t >> 6][S::NV + i] = mv;
       }
     }
     __syncthreads();
     if (t < 5) {
-      const int w = t < 2 ? 0 : 4, i = t < 2 ? t : t - 2;
-      double sv = red[w][i], mv = red[w][3 + i];
-      for (int k = 1; k < 4; ++k) {
+      // the first wave of variable t, and its place among that wave's
+      const int w = S::NV == 3 ? (t < 2 ? 0 : WV) : t < 4 ? t : 3;
+      const int i = t - S::v0(64 * w);
+      double sv = red[w][i], mv = red[w][S::NV + i];
+      for (int k = 1; k < WV; ++k) {
         sv += red[w + k][i];
-        mv = max_nan(mv, red[w + k][3 + i]);
+        mv = max_nan(mv, red[w + k][S::NV + i]);
       }
       A.norm_part[(long long)lt * 10 + t] = sv;
       A.norm_part[(long long)lt * 10 + 5 + t] = mv;
     }
   }
   if constexpr (LAMMAX) {
-    double* up = reinterpret_cast<double*>(&sPr[0][0]);   // the upper three variables' updates
-    double* red = up + 3 * NOWN;
-    if (!owner) {
+    double(*up)[NOWN] = reinterpret_cast<double(*)[NOWN]>(&sPr[0][0]);   // the updates
+    double* red = &up[5][0];
 #pragma unroll
-      for (int i = 0; i < 3; ++i) up[i * NOWN + o] = qn[i];
-    }
+    for (int i = 0; i < S::NV; ++i)
+      if (i < nv) up[v0 + i][o] = qn[i];
     __syncthreads();
     if (owner) {
       double lam = 0.0;
       if (mine) {
-        const double qf[5] = {qn[0], qn[1], up[o], up[NOWN + o], up[2 * NOWN + o]};
+        const double qf[5] = {up[0][o], up[1][o], up[2][o], up[3][o], up[4][o]};
         lam = lambda_sum(qf, m, J, ph.gamma);
       }
       lam = wave_max(lam);
       if ((t & 63) == 63) red[t >> 6] = lam;
     }
     __syncthreads();
-    if (t == 0) A.lam_part[lt] = max_nan(max_nan(red[0], red[1]), max_nan(red[2], red[3]));
+    if (t == 0) {
+      double lam = red[0];
+      for (int k = 1; k < WV; ++k) lam = max_nan(lam, red[k]);
+      A.lam_part[lt] = lam;
+    }
+  }
+}
+
+template <typename S>
+void launch_shape(const StageArgs& a, bool f32, const int* flag, int stage, bool last, int nbricks, hipStream_t st) {
+  const dim3 grid(nbricks), block(S::NT);
+  if (!f32) {
+    if (stage == 0) hipLaunchKernelGGL((brick_kernel<S, double, double, double, false, 1>), grid, block, 0, st, a, flag);
+    else if (last) hipLaunchKernelGGL((brick_kernel<S, double, double, double, false, 2>), grid, block, 0, st, a, flag);
+    else hipLaunchKernelGGL((brick_kernel<S, double, double, double, false, 0>), grid, block, 0, st, a, flag);
+  } else if (stage == 0) {
+    if (a.ref) hipLaunchKernelGGL((brick_kernel<S, float, double, float, true, 9>), grid, block, 0, st, a, flag);
+    else hipLaunchKernelGGL((brick_kernel<S, float, double, float, true, 1>), grid, block, 0, st, a, flag);
+  } else if (last) {
+    hipLaunchKernelGGL((brick_kernel<S, float, float, double, true, 2>), grid, block, 0, st, a, flag);
+  } else {
+    if (a.ref) hipLaunchKernelGGL((brick_kernel<S, float, float, float, true, 8>), grid, block, 0, st, a, flag);
+    else hipLaunchKernelGGL((brick_kernel<S, float, float, float, true, 0>), grid, block, 0, st, a, flag);
   }
 }
 
 }  // namespace
 
-// One stage over the bricks of a block that allows the FAST form: stage 0
-// writes the norm partials of its bricks, the last one (last) the spectral
-// radii.  At least two stages.
-hipError_t launch_brick(const StageArgs& a, bool f32, const int* flag, int stage, bool last, int nbricks, hipStream_t st) {
-  const dim3 grid(nbricks), block(NT);
-  if (!f32) {
-    if (stage == 0) hipLaunchKernelGGL((brick_kernel<double, double, double, false, 1>), grid, block, 0, st, a, flag);
-    else if (last) hipLaunchKernelGGL((brick_kernel<double, double, double, false, 2>), grid, block, 0, st, a, flag);
-    else hipLaunchKernelGGL((brick_kernel<double, double, double, false, 0>), grid, block, 0, st, a, flag);
-  } else if (stage == 0) {
-    if (a.ref) hipLaunchKernelGGL((brick_kernel<float, double, float, true, 9>), grid, block, 0, st, a, flag);
-    else hipLaunchKernelGGL((brick_kernel<float, double, float, true, 1>), grid, block, 0, st, a, flag);
-  } else if (last) {
-    hipLaunchKernelGGL((brick_kernel<float, float, double, true, 2>), grid, block, 0, st, a, flag);
-  } else {
-    if (a.ref) hipLaunchKernelGGL((brick_kernel<float, float, float, true, 8>), grid, block, 0, st, a, flag);
-    else hipLaunchKernelGGL((brick_kernel<float, float, float, true, 0>), grid, block, 0, st, a, flag);
-  }
+// One stage over the bricks (small or wide ones) of a block that allows the
+// FAST form: stage 0 writes the norm partials of its bricks, the last one
+// (last) the spectral radii.  At least two stages.
+hipError_t launch_brick(const StageArgs& a, bool f32, const int* flag, int stage, bool last, bool small, int nbricks,
+                        hipStream_t st) {
+  if (small) launch_shape<SmallBrick>(a, f32, flag, stage, last, nbricks, st);
+  else launch_shape<WideBrick>(a, f32, flag, stage, last, nbricks, st);
   return hipGetLastError();
 }
 

@@ -81,6 +81,7 @@ struct Tiling {
 
 // Bricks of owned nodes of the brick kernel (small blocks).
 constexpr int kBrickI = 8, kBrickJ = 8, kBrickK = 4;
+constexpr int kSmallBrick = 4;   // those of the smallest, in each direction
 
 struct StageArgs {
   const void* qin;      // stencil input Q(k-1), node-major (double or float)

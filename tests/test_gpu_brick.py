@@ -49,6 +49,21 @@ def test_periodic_bricks_equal_the_march(B, prec, dims):
 
 
 @pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("dims", [(4, 4, 4), (5, 5, 5), (3, 9, 13), (31, 32, 29), (32, 33, 29), (45, 37, 22)])
+@pytest.mark.parametrize("bc", [(0,) * 6, (1, 2, 2, 2, 2, 2), (0, 0, 2, 2, 0, 0)])
+def test_small_and_wide_bricks_equal_the_march(B, prec, dims, bc):
+    """Edges and remainders of 4 x 4 x 4 bricks (up to 512 of them) and of
+    8 x 8 x 4 ones, periodic and with bounded directions."""
+    if any(bc) and min(dims) < 9:
+        pytest.skip("a bounded direction needs its boundary layers and stencil")
+    print(f"[gpu-case] bricks small and wide precision={prec} {dims} {bc}", flush=True)
+    g = I.uniform_box(*dims)
+    q = I.jet_state(g, 1.4, seed=sum(dims))
+    kw = dict(precision=prec, bc=bc)
+    _same(_run(B, dims, g.metrics, q, 2, **kw), _run(B, dims, g.metrics, q, 2, **kw, **TILE[prec]))
+
+
+@pytest.mark.parametrize("prec", [0, 1])
 @pytest.mark.parametrize("dims", [(45, 20, 37), (13, 9, 11)])
 def test_curvilinear_bricks_equal_the_march(B, prec, dims):
     """Every metric component nonzero, strong noise: any multiply-add that one
