@@ -2201,11 +2201,11 @@ int dom_build_launch_tables(jz_domain* D) {
     HIP_TRY(hipMalloc((void**)&D->d_jobs, jobs.size() * sizeof(HaloJob)));
     HIP_TRY(hipMemcpy(D->d_jobs, jobs.data(), jobs.size() * sizeof(HaloJob), hipMemcpyHostToDevice));
   }
-  // Batched stage launches (FP64): every part shares the tile shape.  The
-  // FP32-flux batch kernel keeps the primitive ring and reads the metrics
-  // again in its first and last stages, which costs more than the tails of
-  // one launch per part (split 2 x 2 at 512 x 256 x 256: 11 % against 10 %
-  // over the unsplit block); in FP64 the batched launch took the overhead
+  // Batched stage launches (FP64): every part shares the tile shape.  FP32-flux
+  // parts are launched one by one: the batch kernel, when it still exchanged
+  // all its primitives through LDS, cost more than the tails of a launch per
+  // part (split 2 x 2 at 512 x 256 x 256: 11 % against 10 % over the unsplit
+  // block); in FP64 the batched launch took the overhead
   // from 13 % to 6 % (5 % with the row-wise xi copies and the two-level
   // step reductions).
   D->bx = D->sub[0]->tl.bx;
