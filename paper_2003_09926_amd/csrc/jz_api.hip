@@ -229,13 +229,12 @@ void pick_tiling_for_device(int ni, int nj, int nk, const jz_params* p, Tiling* 
 // left to the library.  A tile marches its chunk and about four planes' worth
 // of warm-up and set-up; a round of one tile per workgroup slot takes that
 // long, and a last round that leaves half of every CU idle (two slots each)
-// about 0.7 of it.  So many short chunks pay where the tiles alone leave CUs
+// about 0.6 of it (0.7 if it is the only one).  So many short chunks pay where the tiles alone leave CUs
 // idle, and a number of chunks that fills the last round elsewhere.  Measured
 // steps with the chunks of pick_tiling_for_device / with these: FP64
 // 64 x 48 x 48 146 (8 planes) / 92 us (3), 96 x 64 x 96 207 (8) / 197 (7),
-// 192 x 192 x 192 2134 (64) / 1841 (24; 1790 with 48, which counts as 88 plane
-// times against 84), 320 x 160 x 160 2607 (64) / 2230 (32), 400 x 200 x 200
-// 4563 (64) / 4016 (34); FP32-flux 96 x 64 x 96 175 (8) / 137 (5),
+// 192 x 192 x 192 2134 (64) / 1790 (48), 320 x 160 x 160 2607 (64) / 2230 (32),
+// 400 x 200 x 200 4563 (64) / 4016 (34); FP32-flux 96 x 64 x 96 175 (8) / 137 (5),
 // 128 x 64 x 96 177 (8) / 155 (6).  (A block in a batch keeps the other
 // chunks, and so does one whose tile shape is given: its RMS norms are those
 // it has in a batch.)
@@ -244,13 +243,13 @@ int own_kchunk(const Tiling& t, int ek, bool compact, int most) {
   if (slots < 1) return t.kchunk;
   int best = t.kchunk;
   double least = 0;
-  for (int n = 1; n <= ek; ++n) {
+  const int n0 = compact ? (ek + 63) / 64 : 1;  // (longer ones measured slower, 128 planes 6 % on 512 x 256 x 256)
+  for (int n = n0; n <= ek && n < n0 + 4096; ++n) {
     const int kc = (ek + n - 1) / n;
     const long long blocks = tiles * ((ek + kc - 1) / kc);
     if (blocks > most) break;
-    if (compact && kc > 64) continue;  // (longer ones measured slower, 128 planes 6 % on 512 x 256 x 256)
     const long long full = blocks / slots, rest = blocks % slots;
-    const double rounds = full + (rest == 0 ? 0.0 : t.per_cu > 1 && rest <= slots / t.per_cu ? 0.7 : 1.0);
+    const double rounds = full + (rest == 0 ? 0.0 : t.per_cu == 1 || rest > slots / t.per_cu ? 1.0 : full ? 0.6 : 0.7);
     const double cost = rounds * (kc + 4);
     if (least == 0 || cost < least) {
       best = kc;
