@@ -633,9 +633,8 @@ hipError_t launch_status(const Clock* clk, int* flag, int* verdict, bool reset, 
 
 hipError_t launch_soa_to_nodes(const double* src, double* dst, long long N, int C, hipStream_t st) {
   const dim3 grid(grid_stride_blocks(N)), block(TR_T);
-  if (C == 5) hipLaunchKernelGGL(soa_to_nodes_kernel<5>, grid, block, 0, st, src, dst, N);
-  else if (C == 10) hipLaunchKernelGGL(soa_to_nodes_kernel<10>, grid, block, 0, st, src, dst, N);
-  else return hipErrorInvalidValue;
+  if (C != 10) return hipErrorInvalidValue;  // (a state is taken by take_state_kernel)
+  hipLaunchKernelGGL(soa_to_nodes_kernel<10>, grid, block, 0, st, src, dst, N);
   return hipGetLastError();
 }
 
